@@ -41,7 +41,7 @@ namespace pm {
 pm_status check_device(const pm_graph *g);
 int sampler_cu_count(int dev);
 pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipStream_t s,
-                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, hipStream_t));
+                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, uint64_t *, hipStream_t));
 
 namespace {
 
@@ -332,13 +332,13 @@ __global__ __launch_bounds__(kBlock) void k_sample_alias(SamplerView g, const Al
                                                          uint64_t seed, uint64_t first, uint64_t k,
                                                          unsigned long long *__restrict__ tally)
 {
-    uint32_t cnt[PM_NUM_TALLIES];
-#pragma unroll
-    for (int c = 0; c < PM_NUM_TALLIES; ++c) cnt[c] = 0;
-    const uint64_t nthreads = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += nthreads)
-        tally_add(cnt, alias_sample<CENTERED>(g, T, N, seed, first + i));
-    tally_flush(cnt, tally);
+    WaveTally cnt;
+    const uint64_t step = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t base = wave_index(blockIdx.x) * kWave; base < k; base += step) {  // wave-uniform
+        const uint64_t i = base + (uint64_t)lane_id();
+        tally_count(cnt, i < k ? alias_sample<CENTERED>(g, T, N, seed, first + i) : kUndecided);
+    }
+    tally_flush(cnt, tally, nullptr);
 }
 
 // Draw order for the alias draw: the key is the top bits of the bucket b (the
@@ -360,12 +360,13 @@ __global__ __launch_bounds__(kBlock) void k_sample_alias_sorted(SamplerView g, c
                                                                 const uint32_t *__restrict__ ids,
                                                                 unsigned long long *__restrict__ tally)
 {
-    uint32_t cnt[PM_NUM_TALLIES];
-#pragma unroll
-    for (int c = 0; c < PM_NUM_TALLIES; ++c) cnt[c] = 0;
-    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < k; j += (uint64_t)gridDim.x * blockDim.x)
-        tally_add(cnt, alias_sample<CENTERED>(g, T, N, seed, first + ids[j]));
-    tally_flush(cnt, tally);
+    WaveTally cnt;
+    const uint64_t step = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t base = wave_index(blockIdx.x) * kWave; base < k; base += step) {  // wave-uniform
+        const uint64_t j = base + (uint64_t)lane_id();
+        tally_count(cnt, j < k ? alias_sample<CENTERED>(g, T, N, seed, first + ids[j]) : kUndecided);
+    }
+    tally_flush(cnt, tally, nullptr);
 }
 
 // Buffers of one alias draw-order sort chunk of min(k, kSortedChunk) ids.
@@ -443,7 +444,7 @@ pm_status launch_alias(const pm_graph *g, bool centered, uint64_t seed, uint64_t
     return PM_OK;
 }
 
-pm_status sample_alias_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, hipStream_t s)
+pm_status sample_alias_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *, hipStream_t s)
 {
     if ((g->R_tau && !g->alias_tau) || (g->R_lam && !g->alias_lam)) {
         set_error("alias draw: the graph has no alias tables (pm_graph_build_alias)");

@@ -60,19 +60,23 @@ __global__ __launch_bounds__(kBlock) void k_sample_batch(const BatchGraph *__res
         __syncthreads();  // every thread has read s_tile before it is reused
         if (t >= ntiles) break;  // every block leaves once all its lists are exhausted
         const BatchTile T = tiles[t];
-        uint32_t cnt[PM_NUM_TALLIES];
-#pragma unroll
-        for (int c = 0; c < PM_NUM_TALLIES; ++c) cnt[c] = 0;
+        WaveTally cnt;
+        const uint32_t w0 = (uint32_t)wave_index(0) * kWave;
         if (T.tag == 0) {
             const SamplerView &g = graphs[T.graph].v[0];
-            for (uint32_t i = threadIdx.x; i < T.count; i += blockDim.x)
-                tally_add(cnt, sample_class<false>(g, T.seed, T.first + i));
+            for (uint32_t base = w0; base < T.count; base += kBlock) {  // wave-uniform
+                const uint32_t i = base + (uint32_t)lane_id();
+                tally_count(cnt, i < T.count ? sample_class<false>(g, T.seed, T.first + i) : kUndecided);
+            }
         } else {
             const SamplerView &g = graphs[T.graph].v[1];
-            for (uint32_t i = threadIdx.x; i < T.count; i += blockDim.x)
-                tally_add(cnt, sample_class<true>(g, T.seed, T.first + i));
+            for (uint32_t base = w0; base < T.count; base += kBlock) {
+                const uint32_t i = base + (uint32_t)lane_id();
+                tally_count(cnt, i < T.count ? sample_class<true>(g, T.seed, T.first + i) : kUndecided);
+            }
         }
-        tally_flush(cnt, tallies + ((uint64_t)T.slot * 2 + T.tag) * PM_NUM_TALLIES);
+        // (the barriers of the next tile's fetch keep its counts apart from these)
+        tally_flush(cnt, tallies + ((uint64_t)T.slot * 2 + T.tag) * PM_NUM_TALLIES, nullptr);
     }
 }
 

@@ -17,24 +17,32 @@ namespace pm {
 static_assert(draw_sort_tiles(kSortedChunk) <= kDsMaxTiles, "a sort chunk fits the draw sort's column scan");
 
 // U samples per lane per round of the grid-stride loop (U > 1 only
-// unrolls the loop; each sample is independent).
+// unrolls the loop; each sample is independent).  Whole waves step together.
 template <bool CENTERED, int U, int SEARCH>
-__global__ __launch_bounds__(kBlock) void k_sample(SamplerView g, uint64_t seed, uint64_t first, uint64_t k,
-                                                   unsigned long long *__restrict__ tally)
+__device__ __forceinline__ void sample_ids(const SamplerView &g, uint64_t seed, uint64_t first, uint64_t k,
+                                           unsigned block, unsigned blocks, WaveTally &cnt)
 {
-    uint32_t cnt[PM_NUM_TALLIES];
-#pragma unroll
-    for (int c = 0; c < PM_NUM_TALLIES; ++c) cnt[c] = 0;
-    const uint64_t nthreads = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (uint64_t base = 0; base < k; base += nthreads * U) {
+    const uint64_t nthreads = (uint64_t)blocks * kBlock;
+    const uint64_t w0 = wave_index(block) * kWave;
+    for (uint64_t base = w0; base < k; base += nthreads * U) {  // wave-uniform
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const uint64_t i = base + (uint64_t)q * nthreads + tid;
-            if (i < k) tally_add(cnt, sample_class<CENTERED, SEARCH>(g, seed, first + i));
+            const uint64_t i = base + (uint64_t)q * nthreads + (uint64_t)lane_id();
+            uint32_t cls = kUndecided;
+            if (i < k) cls = sample_class<CENTERED, SEARCH>(g, seed, first + i);
+            tally_count(cnt, cls);
         }
     }
-    tally_flush(cnt, tally);
+}
+
+template <bool CENTERED, int U, int SEARCH>
+__global__ __launch_bounds__(kBlock) void k_sample(SamplerView g, uint64_t seed, uint64_t first, uint64_t k,
+                                                   unsigned long long *__restrict__ tally,
+                                                   unsigned long long *__restrict__ parts)
+{
+    WaveTally cnt;
+    sample_ids<CENTERED, U, SEARCH>(g, seed, first, k, blockIdx.x, gridDim.x, cnt);
+    tally_flush(cnt, tally, parts);
 }
 
 // The same samples with the adjacency tests done by the wave together
@@ -44,22 +52,52 @@ __global__ __launch_bounds__(kBlock) void k_sample(SamplerView g, uint64_t seed,
 template <bool CENTERED, bool SORTED>
 __global__ __launch_bounds__(kBlock) void k_sample_wave(SamplerView g, uint64_t seed, uint64_t first, uint64_t k,
                                                         const uint32_t *__restrict__ ids,
-                                                        unsigned long long *__restrict__ tally)
+                                                        unsigned long long *__restrict__ tally,
+                                                        unsigned long long *__restrict__ parts)
 {
-    uint32_t cnt[PM_NUM_TALLIES];
-#pragma unroll
-    for (int c = 0; c < PM_NUM_TALLIES; ++c) cnt[c] = 0;
-    const uint64_t lane = (uint64_t)lane_id();
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    WaveTally cnt;
     const uint64_t nwaves = (uint64_t)gridDim.x * blockDim.x / kWave;
-    for (uint64_t base = wave * kWave; base < k; base += nwaves * kWave) {  // wave-uniform
-        const uint64_t j = base + lane;
+    for (uint64_t base = wave_index(blockIdx.x) * kWave; base < k; base += nwaves * kWave) {  // wave-uniform
+        const uint64_t j = base + (uint64_t)lane_id();
         const bool act = j < k;
         const uint64_t id = first + (act ? (SORTED ? (uint64_t)ids[j] : j) : 0ull);
         const uint32_t cls = sample_class_wave<CENTERED>(g, seed, id, act);
-        if (act) tally_add(cnt, cls);
+        tally_count(cnt, act ? cls : kUndecided);
     }
-    tally_flush(cnt, tally);
+    tally_flush(cnt, tally, parts);
+}
+
+// Sums of the blocks' rows of counts: block 0 the 3-path sampler's, block 1
+// the centered one's.
+__global__ __launch_bounds__(1024) void k_tally_sum(const unsigned long long *__restrict__ parts_p, unsigned rows_p,
+                                                    const unsigned long long *__restrict__ parts_c, unsigned rows_c,
+                                                    unsigned long long *__restrict__ tallies)
+{
+    constexpr int kRows = 1024 / PM_NUM_TALLIES;
+    __shared__ unsigned long long s_sum[kRows][PM_NUM_TALLIES];
+    const unsigned long long *parts = blockIdx.x ? parts_c : parts_p;
+    const unsigned rows = blockIdx.x ? rows_c : rows_p;
+    const unsigned c = threadIdx.x % PM_NUM_TALLIES, q = threadIdx.x / PM_NUM_TALLIES;
+    unsigned long long v = 0;
+    for (unsigned i = q; i < rows; i += kRows) v += parts[(uint64_t)i * PM_NUM_TALLIES + c];
+    s_sum[q][c] = v;
+    __syncthreads();
+    for (unsigned h = kRows / 2; h > 0; h >>= 1) {
+        if (q < h) s_sum[q][c] += s_sum[q + h][c];
+        __syncthreads();
+    }
+    if (q == 0) tallies[blockIdx.x * PM_NUM_TALLIES + c] = s_sum[0][c];
+}
+
+// tallies[0..8) and [8..16) (3-path, centered): the sums of the rows of parts_p
+// and parts_c (a sampler that did not run has none)
+static pm_status sum_tallies(const uint64_t *parts_p, unsigned rows_p, const uint64_t *parts_c, unsigned rows_c,
+                      uint64_t *tallies, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_tally_sum, dim3(2), dim3(1024), 0, s, (const unsigned long long *)parts_p, rows_p,
+                       (const unsigned long long *)parts_c, rows_c, (unsigned long long *)tallies);
+    PM_HIP(hipGetLastError());
+    return PM_OK;
 }
 
 // launch shape of the samplers (pm_set_sampler_shape)
@@ -102,15 +140,15 @@ pm_status set_sampler_shape(int32_t samples_per_lane, int32_t blocks_per_cu)
 }
 
 template <bool CENTERED, int U>
-static void launch_k_sample(unsigned blocks, hipStream_t s, const SamplerView &v, uint64_t seed, uint64_t first,
-                            uint64_t k, uint64_t *tally)
+static void launch_k_sample(int mode, unsigned blocks, hipStream_t s, const SamplerView &v, uint64_t seed,
+                            uint64_t first, uint64_t k, unsigned long long *tally, unsigned long long *parts)
 {
-    if (g_search_mode.load() == PM_SEARCH_HASH)
+    if (mode == PM_SEARCH_HASH)
         hipLaunchKernelGGL((k_sample<CENTERED, U, PM_SEARCH_HASH>), dim3(blocks), dim3(kBlock), 0, s, v, seed, first,
-                           k, (unsigned long long *)tally);
+                           k, tally, parts);
     else
         hipLaunchKernelGGL((k_sample<CENTERED, U, PM_SEARCH_LANE>), dim3(blocks), dim3(kBlock), 0, s, v, seed, first,
-                           k, (unsigned long long *)tally);
+                           k, tally, parts);
 }
 
 int sampler_cu_count(int dev)
@@ -126,6 +164,24 @@ int sampler_cu_count(int dev)
     }
     return cache[dev];
 }
+
+// The process-wide settings as one call uses them (read once, so that a
+// setter on another thread cannot change them between its launches).
+struct SampleShape {
+    int per_lane, mode;
+    unsigned cap;  // most blocks of a launch
+    bool order;
+    uint64_t order_min;
+    explicit SampleShape(const pm_graph *g)
+        : per_lane(g_samples_per_lane.load()), mode(g_search_mode.load()),
+          cap((unsigned)(sampler_cu_count(g->device) * g_blocks_per_cu.load())), order(draw_order_enabled()),
+          order_min(draw_order_min())
+    {
+    }
+    // is a sampler of total weight R draw-ordered for k samples, and in one chunk?
+    bool sorted(uint64_t R, uint64_t k) const { return R > 1 && k > 0 && order && k >= order_min; }
+    bool one_chunk(uint64_t R, uint64_t k) const { return sorted(R, k) && k <= kSortedChunk; }
+};
 
 // Draw-ordered sampling.  Tallies are sums over sample ids, so the order in
 // which samples run is free: sorting the ids of a chunk by the top
@@ -149,14 +205,18 @@ struct DrawKey {
 template <bool CENTERED, int SEARCH>
 __global__ __launch_bounds__(kBlock) void k_sample_sorted(SamplerView g, uint64_t seed, uint64_t first, uint64_t k,
                                                           const uint32_t *__restrict__ ids,
-                                                          unsigned long long *__restrict__ tally)
+                                                          unsigned long long *__restrict__ tally,
+                                                          unsigned long long *__restrict__ parts)
 {
-    uint32_t cnt[PM_NUM_TALLIES];
-#pragma unroll
-    for (int c = 0; c < PM_NUM_TALLIES; ++c) cnt[c] = 0;
-    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < k; j += (uint64_t)gridDim.x * blockDim.x)
-        tally_add(cnt, sample_class<CENTERED, SEARCH>(g, seed, first + ids[j]));
-    tally_flush(cnt, tally);
+    WaveTally cnt;
+    const uint64_t step = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t base = wave_index(blockIdx.x) * kWave; base < k; base += step) {  // wave-uniform
+        const uint64_t j = base + (uint64_t)lane_id();
+        uint32_t cls = kUndecided;
+        if (j < k) cls = sample_class<CENTERED, SEARCH>(g, seed, first + ids[j]);
+        tally_count(cnt, cls);
+    }
+    tally_flush(cnt, tally, parts);
 }
 
 // The ids [first, first + kc) sorted by their draw keys in b's buffers
@@ -170,44 +230,52 @@ static pm_status sort_chunk(const SamplerView &v, bool centered, uint64_t seed, 
     return draw_sort("draw_sort", DrawKey{v.R, seed, first, centered ? 1u : 0u, kshift}, kc, kbits, s, b, ids);
 }
 
-// The samples first + ids[j] for j < kc, into tally.
-static pm_status sample_chunk(const SamplerView &v, bool centered, uint64_t seed, uint64_t first, uint64_t kc,
-                              const uint32_t *ids, uint64_t *tally, unsigned blocks, hipStream_t s)
+// blocks of the launch over a sort chunk of kc ids
+static unsigned chunk_blocks(uint64_t kc, unsigned cap)
 {
-    const unsigned kb = (unsigned)std::min<uint64_t>((kc + kBlock - 1) / kBlock, blocks);
-    unsigned long long *t = (unsigned long long *)tally;
+    return (unsigned)std::min<uint64_t>((kc + kBlock - 1) / kBlock, cap);
+}
+
+// The samples first + ids[j] for j < kc, into tally, or as the rows of parts
+// (kb of them) when given.
+static pm_status sample_chunk(const SampleShape &sh, const SamplerView &v, bool centered, uint64_t seed,
+                              uint64_t first, uint64_t kc, const uint32_t *ids, uint64_t *tally, uint64_t *parts,
+                              hipStream_t s)
+{
+    const unsigned kb = chunk_blocks(kc, sh.cap);
+    unsigned long long *t = (unsigned long long *)tally, *q = (unsigned long long *)parts;
     ProfScope pk(centered ? "sample_centered.sorted" : "sample_path.sorted", s);
-    const int mode = g_search_mode.load();
+    const int mode = sh.mode;
     if (mode == PM_SEARCH_WAVE) {
         if (centered)
-            hipLaunchKernelGGL((k_sample_wave<true, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t);
+            hipLaunchKernelGGL((k_sample_wave<true, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t, q);
         else
-            hipLaunchKernelGGL((k_sample_wave<false, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t);
+            hipLaunchKernelGGL((k_sample_wave<false, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t, q);
     } else if (mode == PM_SEARCH_HASH) {
         if (centered)
             hipLaunchKernelGGL((k_sample_sorted<true, PM_SEARCH_HASH>), dim3(kb), dim3(kBlock), 0, s, v, seed, first,
-                               kc, ids, t);
+                               kc, ids, t, q);
         else
             hipLaunchKernelGGL((k_sample_sorted<false, PM_SEARCH_HASH>), dim3(kb), dim3(kBlock), 0, s, v, seed, first,
-                               kc, ids, t);
+                               kc, ids, t, q);
     } else if (centered)
         hipLaunchKernelGGL((k_sample_sorted<true, PM_SEARCH_LANE>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc,
-                           ids, t);
+                           ids, t, q);
     else
         hipLaunchKernelGGL((k_sample_sorted<false, PM_SEARCH_LANE>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc,
-                           ids, t);
+                           ids, t, q);
     PM_HIP(hipGetLastError());
     return PM_OK;
 }
 
-static pm_status launch_sorted_in(const SamplerView &v, bool centered, uint64_t seed, uint64_t first, uint64_t k,
-                                  uint64_t *tally, unsigned blocks, hipStream_t s, const DrawSortBufs &b)
+static pm_status launch_sorted_in(const SampleShape &sh, const SamplerView &v, bool centered, uint64_t seed,
+                                  uint64_t first, uint64_t k, uint64_t *tally, hipStream_t s, const DrawSortBufs &b)
 {
     for (uint64_t c0 = 0; c0 < k; c0 += b.chunk) {
         const uint64_t kc = std::min(b.chunk, k - c0);
         uint32_t *ids = nullptr;
         PM_TRY(sort_chunk(v, centered, seed, first + c0, kc, s, b, &ids));
-        PM_TRY(sample_chunk(v, centered, seed, first + c0, kc, ids, tally, blocks, s));
+        PM_TRY(sample_chunk(sh, v, centered, seed, first + c0, kc, ids, tally, nullptr, s));
     }
     return PM_OK;
 }
@@ -223,52 +291,57 @@ static pm_status sort_bufs(Temps &tmp, uint64_t k, DrawSortBufs *b)
 }
 
 // the draw-ordered launch with its buffers from the stream-ordered allocator
-static pm_status launch_sorted(const SamplerView &v, bool centered, uint64_t seed, uint64_t first, uint64_t k,
-                               uint64_t *tally, unsigned blocks, hipStream_t s)
+static pm_status launch_sorted(const SampleShape &sh, const SamplerView &v, bool centered, uint64_t seed,
+                               uint64_t first, uint64_t k, uint64_t *tally, hipStream_t s)
 {
     Temps tmp(s);
     DrawSortBufs b{};
     PM_TRY(sort_bufs(tmp, k, &b));
-    return launch_sorted_in(v, centered, seed, first, k, tally, blocks, s, b);
+    return launch_sorted_in(sh, v, centered, seed, first, k, tally, s, b);
 }
 
-// One sampler's k samples from id `first` into tally (device, added to).
-// Draw-ordered launches take their buffers from `fixed` when given, else
-// from the allocator.
-static pm_status launch_sampler(const pm_graph *g, bool centered, uint64_t seed, uint64_t first, uint64_t k,
-                                uint64_t *tally, hipStream_t s, const DrawSortBufs *fixed = nullptr)
+// One sampler's k samples from id `first`: into tally (device, added to), or
+// with `parts` (an id-order launch of sh.cap <= kMaxTallyParts), as *rows rows
+// of parts.  Draw-ordered launches take their buffers from `fixed` when
+// given, else from the allocator.
+static pm_status launch_sampler(const SampleShape &sh, const pm_graph *g, bool centered, uint64_t seed,
+                                uint64_t first, uint64_t k, uint64_t *tally, hipStream_t s,
+                                const DrawSortBufs *fixed = nullptr, uint64_t *parts = nullptr,
+                                unsigned *rows = nullptr)
 {
     const SamplerView v = view_of(g, centered);
     if (v.R == 0 || k == 0) return PM_OK;
-    const int U = g_samples_per_lane.load();
+    const bool wave = sh.mode == PM_SEARCH_WAVE;
+    const int U = wave ? 1 : sh.per_lane;
     const uint64_t want = (k + (uint64_t)kBlock * U - 1) / ((uint64_t)kBlock * U);
-    const uint64_t cap = (uint64_t)sampler_cu_count(g->device) * (uint64_t)g_blocks_per_cu.load();
-    const unsigned blocks = (unsigned)std::max<uint64_t>(1, std::min(want, cap));
+    const unsigned blocks = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(want, sh.cap));
     ProfScope prof(centered ? "sample_centered" : "sample_path", s);
-    if (k >= draw_order_min() && v.R > 1 && draw_order_enabled())
-        return fixed ? launch_sorted_in(v, centered, seed, first, k, tally, (unsigned)cap, s, *fixed)
-                     : launch_sorted(v, centered, seed, first, k, tally, (unsigned)cap, s);
-    if (g_search_mode.load() == PM_SEARCH_WAVE) {
-        const uint64_t wants = (k + kBlock - 1) / kBlock;
-        const unsigned wb = (unsigned)std::max<uint64_t>(1, std::min(wants, cap));
-        if (centered)
-            hipLaunchKernelGGL((k_sample_wave<true, false>), dim3(wb), dim3(kBlock), 0, s, v, seed, first, k, nullptr,
-                               (unsigned long long *)tally);
-        else
-            hipLaunchKernelGGL((k_sample_wave<false, false>), dim3(wb), dim3(kBlock), 0, s, v, seed, first, k,
-                               nullptr, (unsigned long long *)tally);
+    if (sh.sorted(v.R, k))
+        return fixed ? launch_sorted_in(sh, v, centered, seed, first, k, tally, s, *fixed)
+                     : launch_sorted(sh, v, centered, seed, first, k, tally, s);
+    unsigned long long *t = (unsigned long long *)tally, *q = (unsigned long long *)parts;
+    if (parts) *rows = blocks;  // k <= kMaxLaunchSamples then: one launch
+    for (uint64_t at = 0; at < k; at += kMaxLaunchSamples) {
+        const uint64_t id = first + at, kc = std::min(k - at, kMaxLaunchSamples);
+        if (wave) {
+            if (centered)
+                hipLaunchKernelGGL((k_sample_wave<true, false>), dim3(blocks), dim3(kBlock), 0, s, v, seed, id, kc,
+                                   nullptr, t, q);
+            else
+                hipLaunchKernelGGL((k_sample_wave<false, false>), dim3(blocks), dim3(kBlock), 0, s, v, seed, id, kc,
+                                   nullptr, t, q);
+        } else {
+            switch (U * 2 + (centered ? 1 : 0)) {
+            case 2: launch_k_sample<false, 1>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
+            case 3: launch_k_sample<true, 1>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
+            case 4: launch_k_sample<false, 2>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
+            case 5: launch_k_sample<true, 2>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
+            case 8: launch_k_sample<false, 4>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
+            default: launch_k_sample<true, 4>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
+            }
+        }
         PM_HIP(hipGetLastError());
-        return PM_OK;
     }
-    switch (U * 2 + (centered ? 1 : 0)) {
-    case 2: launch_k_sample<false, 1>(blocks, s, v, seed, first, k, tally); break;
-    case 3: launch_k_sample<true, 1>(blocks, s, v, seed, first, k, tally); break;
-    case 4: launch_k_sample<false, 2>(blocks, s, v, seed, first, k, tally); break;
-    case 5: launch_k_sample<true, 2>(blocks, s, v, seed, first, k, tally); break;
-    case 8: launch_k_sample<false, 4>(blocks, s, v, seed, first, k, tally); break;
-    default: launch_k_sample<true, 4>(blocks, s, v, seed, first, k, tally); break;
-    }
-    PM_HIP(hipGetLastError());
     return PM_OK;
 }
 
@@ -352,12 +425,6 @@ pm_status draw_order(const pm_graph *g, int32_t centered, uint64_t seed, uint64_
     return PM_OK;
 }
 
-// Is a sampler's launch draw-ordered in a single sort chunk?
-static bool one_sorted_chunk(const SamplerView &v, uint64_t k)
-{
-    return v.R > 1 && k > 0 && k >= draw_order_min() && draw_order_enabled() && k <= kSortedChunk;
-}
-
 // Both samplers draw-ordered in one chunk each: the centered sampler's keys
 // are drawn and sorted on a side stream while the caller's stream sorts the
 // 3-path sampler's; the side stream joins s before the 3-path samples, and
@@ -366,10 +433,10 @@ static bool one_sorted_chunk(const SamplerView &v, uint64_t k)
 // (sorting the centered ids beside the 3-path sampling kernel instead slows
 // that kernel by more than it saves).  Each sampler runs the same kernels on
 // the same ids as in sequence, so the tallies are the same.
-static pm_status sample_pair_overlapped(const pm_graph *g, const pm_params *p, uint64_t *tallies, hipStream_t s)
+static pm_status sample_pair_overlapped(const SampleShape &sh, const pm_graph *g, const pm_params *p,
+                                        uint64_t *tallies, uint64_t *const parts[2], unsigned rows[2], hipStream_t s)
 {
     const SamplerView vp = view_of(g, false), vc = view_of(g, true);
-    const unsigned cap = (unsigned)((uint64_t)sampler_cu_count(g->device) * (uint64_t)g_blocks_per_cu.load());
     Temps tmp(s);
     DrawSortBufs bp{}, bc{};
     PM_TRY(sort_bufs(tmp, p->k_path, &bp));
@@ -387,12 +454,44 @@ static pm_status sample_pair_overlapped(const pm_graph *g, const pm_params *p, u
         // slows it by more than the join costs
         PM_HIP(fork.join());
     }
+    rows[0] = chunk_blocks(p->k_path, sh.cap);
+    rows[1] = chunk_blocks(p->k_cent, sh.cap);
     {
         ProfScope prof("sample_path", s);
-        PM_TRY(sample_chunk(vp, false, p->seed, p->first_id_path, p->k_path, ids_p, tallies, cap, s));
+        PM_TRY(sample_chunk(sh, vp, false, p->seed, p->first_id_path, p->k_path, ids_p, tallies, parts[0], s));
     }
     ProfScope prof("sample_centered", s);
-    return sample_chunk(vc, true, p->seed, p->first_id_cent, p->k_cent, ids_c, tallies + PM_NUM_TALLIES, cap, s);
+    return sample_chunk(sh, vc, true, p->seed, p->first_id_cent, p->k_cent, ids_c, tallies + PM_NUM_TALLIES,
+                        parts[1], s);
+}
+
+// Both samplers' tallies into tallies_dev[2 x PM_NUM_TALLIES].  `scratch`,
+// when given, holds 2 x kMaxTallyParts rows of block counts: where every
+// sampler is one launch of at most so many blocks, the blocks store their
+// counts there and one kernel sums them, so that no launch ends in atomics on
+// one line (a caller without it, whose launches may be captured in a graph,
+// gets one atomic per block and class).
+static pm_status sample_into(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *scratch,
+                             hipStream_t s)
+{
+    PM_TRY(check_device(g));
+    const SampleShape sh(g);
+    const bool pair = sh.one_chunk(g->R_tau, p->k_path) && sh.one_chunk(g->R_lam, p->k_cent);
+    if (sh.cap > kMaxTallyParts || std::max(p->k_path, p->k_cent) > kMaxLaunchSamples ||
+        (!pair && (sh.sorted(g->R_tau, p->k_path) || sh.sorted(g->R_lam, p->k_cent))))
+        scratch = nullptr;
+    if (!scratch) PM_TRY(fill_async<uint64_t>(tallies_dev, 0ull, 2 * PM_NUM_TALLIES, s));
+    uint64_t *const parts[2] = {scratch, scratch ? scratch + kMaxTallyParts * PM_NUM_TALLIES : nullptr};
+    unsigned rows[2] = {0, 0};
+    if (pair) {
+        PM_TRY(sample_pair_overlapped(sh, g, p, tallies_dev, parts, rows, s));
+    } else {
+        PM_TRY(launch_sampler(sh, g, false, p->seed, p->first_id_path, p->k_path, tallies_dev, s, nullptr, parts[0],
+                              &rows[0]));
+        PM_TRY(launch_sampler(sh, g, true, p->seed, p->first_id_cent, p->k_cent, tallies_dev + PM_NUM_TALLIES, s,
+                              nullptr, parts[1], &rows[1]));
+    }
+    return scratch ? sum_tallies(parts[0], rows[0], parts[1], rows[1], tallies_dev, s) : PM_OK;
 }
 
 pm_status sample_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, hipStream_t s)
@@ -401,13 +500,7 @@ pm_status sample_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_
         set_error("null argument");
         return PM_EINVAL;
     }
-    PM_TRY(check_device(g));
-    PM_TRY(fill_async<uint64_t>(tallies_dev, 0ull, 2 * PM_NUM_TALLIES, s));
-    if (one_sorted_chunk(view_of(g, false), p->k_path) && one_sorted_chunk(view_of(g, true), p->k_cent))
-        return sample_pair_overlapped(g, p, tallies_dev, s);
-    PM_TRY(launch_sampler(g, false, p->seed, p->first_id_path, p->k_path, tallies_dev, s));
-    PM_TRY(launch_sampler(g, true, p->seed, p->first_id_cent, p->k_cent, tallies_dev + PM_NUM_TALLIES, s));
-    return PM_OK;
+    return sample_into(g, p, tallies_dev, nullptr, s);
 }
 
 __global__ void k_philox(const uint32_t *in, uint32_t *out, int64_t count)
@@ -540,9 +633,10 @@ pm_status check_device(const pm_graph *g)
 }
 
 // Run both samplers of one graph through `run` (which fills 2 x PM_NUM_TALLIES
-// device tallies), read the tallies back and finalize.
+// device tallies, with 2 x kMaxTallyParts rows of scratch), read the tallies
+// back and finalize.
 pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipStream_t s,
-                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, hipStream_t))
+                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, uint64_t *, hipStream_t))
 {
     if (!g || !p || !out) {
         set_error("null argument");
@@ -558,9 +652,9 @@ pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipS
     }
     PM_TRY(check_device(g));
     uint64_t *t = nullptr;
-    PM_TRY(dev_alloc((void **)&t, 2 * PM_NUM_TALLIES * sizeof(uint64_t), s));
+    PM_TRY(dev_alloc((void **)&t, 2 * (kMaxTallyParts + 1) * PM_NUM_TALLIES * sizeof(uint64_t), s));
     uint64_t host[2 * PM_NUM_TALLIES];
-    pm_status st = run(g, p, t, s);
+    pm_status st = run(g, p, t, t + 2 * PM_NUM_TALLIES, s);
     if (st == PM_OK) {
         hipError_t e = hipMemcpyAsync(host, t, sizeof(host), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -577,7 +671,7 @@ pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipS
 
 pm_status count_on_graph(const pm_graph *g, const pm_params *p, pm_result *out, hipStream_t s)
 {
-    return count_with(g, p, out, s, sample_async);
+    return count_with(g, p, out, s, sample_into);
 }
 
 // ---------------------------------------------------------------------------
@@ -645,8 +739,9 @@ pm_status count_noalloc(const pm_graph *g, const pm_params *p, pm_result *out, h
     draw_sort_carve(base + kStaticTallyBytes, kStaticChunk, &b);
     // the tallies keep the last call's contents: clear them (a fill kernel)
     PM_TRY(fill_async<uint64_t>(tally, 0ull, 2 * PM_NUM_TALLIES, s));
-    PM_TRY(launch_sampler(g, false, p->seed, p->first_id_path, p->k_path, tally, s, &b));
-    PM_TRY(launch_sampler(g, true, p->seed, p->first_id_cent, p->k_cent, tally + PM_NUM_TALLIES, s, &b));
+    const SampleShape sh(g);
+    PM_TRY(launch_sampler(sh, g, false, p->seed, p->first_id_path, p->k_path, tally, s, &b));
+    PM_TRY(launch_sampler(sh, g, true, p->seed, p->first_id_cent, p->k_cent, tally + PM_NUM_TALLIES, s, &b));
     uint64_t host[2 * PM_NUM_TALLIES];
     hipError_t e = hipMemcpyAsync(host, tally, sizeof(host), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
