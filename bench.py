@@ -59,9 +59,9 @@ def load_traffic():
 
 def rev_pass_bytes(n: int) -> float:
     """Algorithmic bytes per element of one reverse-sort scatter launch,
-    averaged over its passes (8-bit digits over the bits of n - 1)."""
+    averaged over its passes (11-bit digits over the bits of n - 1)."""
     bits = max(int(n - 1).bit_length(), 1)
-    passes = (bits + 7) // 8
+    passes = (bits + 10) // 11
     if passes == 1:
         return 8.0  # key read, value written
     per = [12.0] + [16.0] * (passes - 2) + [12.0]

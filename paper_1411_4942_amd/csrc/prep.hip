@@ -1229,7 +1229,7 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     PM_TRY(tmp.get(&vk1, nn));
     PM_TRY(tmp.get(&vv1, nn));
     uint32_t *sorted_deg, *order;
-    PM_TRY(radix_sort("vertex_sort", deg_in, nullptr, vk0, vv0, vk1, vv1, n, bits_for((uint64_t)g->dmax), rscr, s,
+    PM_TRY(radix_sort("vertex_sort", RadixKeys{deg_in}, vk0, vv0, vk1, vv1, n, bits_for((uint64_t)g->dmax), rscr, s,
                       &sorted_deg, &order));
 
     PM_TRY(dev_alloc((void **)&g->rank, sizeof(int32_t) * nn, s));
@@ -1421,8 +1421,8 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     // reverse slots and the symmetry check: the slots' columns sorted stably,
     // with each slot's own position as payload (only the payload is kept)
     uint32_t *keys_unused, *rev;
-    PM_TRY(radix_sort("reverse_sort", g->col, nullptr, kb, vfree, ka, v2a, slots, vbits, rscr, s, &keys_unused, &rev,
-                      nullptr, nullptr, false));
+    PM_TRY(radix_sort("reverse_sort", RadixKeys{g->col}, kb, vfree, ka, v2a, slots, vbits, rscr, s, &keys_unused,
+                      &rev, false));
     Fork hfork2(s, hside, 1);  // the side stream now also waits for the reverse sort
     PM_HIP(hfork2.status);
     PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hside[0], kRowHashWide));
