@@ -27,6 +27,7 @@
 namespace pm {
 
 pm_status check_device(const pm_graph *g);
+int sampler_cu_count(int dev);
 
 namespace {
 
@@ -92,26 +93,127 @@ __device__ __forceinline__ unsigned __int128 wave_sum128(unsigned __int128 v)
     return v;
 }
 
-// split[x] = number of neighbours of x below x (rows ascending)
-__global__ __launch_bounds__(kBlock) void k_split(const uint32_t *__restrict__ off, const uint32_t *__restrict__ col,
-                                                  int64_t n, uint32_t *__restrict__ split)
+// One value per thread summed over the block and added to *dst, one atomic per
+// block (an atomic per wave on these few words cost 5.9 ns each).  Every
+// thread of the block calls it; s_w holds THREADS / kWave words.
+template <int THREADS>
+__device__ __forceinline__ void block_add(unsigned long long v, unsigned long long *s_w, unsigned long long *dst)
 {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
-        int64_t lo = off[x], hi = off[x + 1];
-        const int64_t a = lo;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (col[mid] < (uint32_t)x)
-                lo = mid + 1;
-            else
-                hi = mid;
-        }
-        split[x] = (uint32_t)(lo - a);
+    v = wave_sum_u64(v);
+    __syncthreads();  // s_w may still be read by an earlier call
+    if (lane_id() == 0) s_w[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int w = 0; w < THREADS / kWave; ++w) t += s_w[w];
+        if (t) atomicAdd(dst, t);
     }
 }
 
+// The vertices by the kernels that handle them.  Triangles and 4-cliques:
+// classes by forward degree D.  4-cycles: classes by S, the sum of the degrees
+// of x's lower neighbours (at least the wedges counted at x), which bounds the
+// distinct ids a table must hold.
+enum : int { kCl64, kCl256, kCl1024, kClMore, kC4Wave, kC4Block, kC4Big, kC4Ranges, kExactClasses };
+constexpr uint32_t kC4WaveMax = 384;    // wedges: tables of 512, 4096 and 16384 slots, at most 3/4 full
+constexpr uint32_t kC4BlockMax = 3072;
+constexpr uint32_t kC4BigMax = 12288;
+
+// Counters on lines of their own, and the largest forward degree.
+struct ExactLists {
+    struct alignas(128) Line {
+        uint32_t n;
+    };
+    Line count[kExactClasses];
+    Line dmax;
+};
+
+// Class c's list lies in array c / 2 of n words: even classes from the front,
+// odd ones from the back (a vertex is in at most one class of each pair).
+__device__ __forceinline__ uint32_t list_at(const uint32_t *__restrict__ lists, int64_t n, int c, uint32_t i)
+{
+    const uint32_t *a = lists + (int64_t)(c / 2) * n;
+    return c & 1 ? a[n - 1 - i] : a[i];
+}
+
+// split[x] = number of neighbours of x below x (rows ascending), and the
+// lists.  A block takes kBlock vertices, highest ids (the heaviest) first:
+// 16 lanes per vertex find its split and sum its lower neighbours' degrees,
+// highest first, until they pass kC4BigMax; then a thread per vertex appends
+// it, one atomic per class and block.
+constexpr int kClassLanes = 16;
+
+__global__ __launch_bounds__(kBlock) void k_classify(const uint32_t *__restrict__ off, const uint32_t *__restrict__ col,
+                                                     int64_t n, uint32_t *__restrict__ split,
+                                                     uint32_t *__restrict__ lists, ExactLists *L)
+{
+    __shared__ uint32_t s_split[kBlock], s_deg[kBlock], s_sum[kBlock];
+    __shared__ uint32_t s_n[kExactClasses], s_base[kExactClasses];
+    __shared__ uint32_t s_dmax;
+    const int t = threadIdx.x, sub = t & (kClassLanes - 1);
+    if (t < kExactClasses) s_n[t] = 0;
+    if (t == 0) s_dmax = 0;
+    for (int r = 0; r < kClassLanes; ++r) {
+        const int q = r * (kBlock / kClassLanes) + t / kClassLanes;
+        const int64_t x = n - 1 - ((int64_t)blockIdx.x * kBlock + q);
+        uint32_t sp = 0, d = 0, sum = 0;
+        if (x >= 0) {
+            const uint32_t a = off[x], e = off[x + 1];
+            d = e - a;
+            uint32_t lo = a, hi = e;
+            while (lo < hi) {  // the same steps in all of the vertex's lanes
+                const uint32_t mid = lo + (hi - lo) / 2;
+                if (col[mid] < (uint32_t)x)
+                    lo = mid + 1;
+                else
+                    hi = mid;
+            }
+            sp = lo - a;
+            for (uint32_t k = 0; k < sp && sum <= kC4BigMax; k += kClassLanes) {
+                uint32_t dw = 0;
+                if (k + sub < sp) {
+                    const uint32_t w = col[a + sp - 1 - (k + sub)];
+                    dw = off[w + 1] - off[w];
+                    dw = dw > kC4BigMax ? kC4BigMax + 1 : dw;
+                }
+#pragma unroll
+                for (int o = kClassLanes / 2; o > 0; o >>= 1) dw += __shfl_xor(dw, o, kClassLanes);
+                sum += dw;
+            }
+        }
+        if (sub == 0) {
+            s_split[q] = sp;
+            s_deg[q] = d;
+            s_sum[q] = sum;
+        }
+    }
+    __syncthreads();
+    const int64_t x = n - 1 - ((int64_t)blockIdx.x * kBlock + t);
+    int cl = -1, c4 = -1;
+    uint32_t icl = 0, ic4 = 0;
+    if (x >= 0) {
+        const uint32_t sp = s_split[t], D = s_deg[t] - sp, S = s_sum[t];
+        split[x] = sp;
+        if (D >= 2) cl = D <= 64 ? kCl64 : D <= 256 ? kCl256 : D <= 1024 ? kCl1024 : kClMore;
+        if (sp >= 2) c4 = S <= kC4WaveMax ? kC4Wave : S <= kC4BlockMax ? kC4Block : S <= kC4BigMax ? kC4Big : kC4Ranges;
+        if (cl >= 0) icl = atomicAdd(&s_n[cl], 1u);
+        if (c4 >= 0) ic4 = atomicAdd(&s_n[c4], 1u);
+        if (D >= 2) atomicMax(&s_dmax, D);
+    }
+    __syncthreads();
+    if (t < kExactClasses && s_n[t]) s_base[t] = atomicAdd(&L->count[t].n, s_n[t]);
+    if (t == kExactClasses && s_dmax) atomicMax(&L->dmax.n, s_dmax);
+    __syncthreads();
+    const auto put = [&](int c, uint32_t i) {
+        uint32_t *a = lists + (int64_t)(c / 2) * n;
+        a[c & 1 ? n - 1 - i : (int64_t)i] = (uint32_t)x;
+    };
+    if (cl >= 0) put(cl, s_base[cl] + icl);
+    if (c4 >= 0) put(c4, s_base[c4] + ic4);
+}
+
 // Triangles and 4-cliques at their lowest vertex u, one u per block at a time
-// (vertices with lo < d+(u) <= 32 W; W words of 32 bits per row).  Row i of
+// (a class's vertices, d+(u) <= 32 W; W words of 32 bits per row).  Row i of
 // the graph induced on N+(u) = {ids[0] < ids[1] < ...} has bit j when
 // ids[i] ~ ids[j], j > i (only forward neighbours are looked up).
 //  - Each bit is a triangle {u, v_i, v_j}, found once.  It adds one to t_e
@@ -129,7 +231,8 @@ constexpr uint32_t kNoId = 0xFFFFFFFFu;  // an empty member-hash slot (vertex id
 template <int W, bool GLOBAL, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_cliques(const uint32_t *__restrict__ off,
                                                     const uint32_t *__restrict__ col,
-                                                    const uint32_t *__restrict__ split, int64_t n, uint32_t lo_d,
+                                                    const uint32_t *__restrict__ split, int64_t n,
+                                                    const uint32_t *__restrict__ lists, int cls, uint32_t count,
                                                     uint32_t hi_d, uint32_t *__restrict__ scratch, uint32_t gslots,
                                                     uint32_t *__restrict__ t_e, ExactAcc *acc)
 {
@@ -141,6 +244,7 @@ __global__ __launch_bounds__(THREADS) void k_cliques(const uint32_t *__restrict_
     __shared__ uint32_t s_rows[kLdsRows];
     __shared__ uint32_t h_key[kSlots];   // member id, or kNoId
     __shared__ uint16_t h_idx[kSlots];   // its index in ids
+    __shared__ unsigned long long s_sum[THREADS / kWave];
     // GLOBAL with gslots > 0: ids, their counters and a member hash of gslots
     // slots (a power of two >= 2 hi_d) in dynamic LDS; gslots = 0: ids and
     // counters in the block's global slice, members found by binary search
@@ -155,9 +259,9 @@ __global__ __launch_bounds__(THREADS) void k_cliques(const uint32_t *__restrict_
     uint16_t *hidx = GLOBAL ? reinterpret_cast<uint16_t *>(dyn + 2ull * hi_d + gslots) : h_idx;
     const int wv = threadIdx.x / kWave, lane = lane_id(), nwv = THREADS / kWave;
     unsigned long long k4 = 0, tri = 0;
-    for (int64_t u = blockIdx.x; u < n; u += gridDim.x) {
-        const uint32_t beg = off[u] + split[u], D = off[u + 1] - beg;
-        if (D <= lo_d || D > hi_d) continue;  // block-uniform
+    for (uint32_t k = blockIdx.x; k < count; k += gridDim.x) {
+        const uint32_t u = list_at(lists, n, cls, k);
+        const uint32_t beg = off[u] + split[u], D = off[u + 1] - beg;  // <= hi_d by the class
         for (uint32_t i = threadIdx.x; i < D; i += THREADS) {
             ids[i] = col[beg + i];
             tri_u[i] = 0;
@@ -232,28 +336,88 @@ __global__ __launch_bounds__(THREADS) void k_cliques(const uint32_t *__restrict_
         }
         __syncthreads();  // the rows are rebuilt for the next u
     }
-    // per-wave sums (a block reduction's LDS would not fit beside the rows)
-    k4 = wave_sum_u64(k4);
-    tri = wave_sum_u64(tri);
-    if (lane == 0 && k4) atomicAdd(&acc->k4, k4);
-    if (lane == 0 && tri) atomicAdd(&acc->tri, tri);
+    block_add<THREADS>(k4, s_sum, &acc->k4);
+    block_add<THREADS>(tri, s_sum, &acc->tri);
 }
 
-// largest forward degree d+(u)
-__global__ __launch_bounds__(kBlock) void k_dplus_max(const uint32_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ split, int64_t n,
-                                                      uint32_t *__restrict__ out)
+// The same for vertices of at most 64 forward neighbours, a wave each: a row
+// is one 64-bit word, and no barrier is needed.  Four members at a time are
+// looked up, 16 lanes walking the forward row of each.  What bounds it is the
+// chain of dependent reads per vertex (its offsets, its row, the members'
+// offsets, their rows), so many waves run at once (7 KiB of LDS per block of
+// four).  A block per vertex, four barriers each, took 2.36 ms on a graph of
+// 1e6 vertices and 1e7 edges, where this takes 1.23 ms.
+constexpr int kClSlots = 128;  // member hash: at most half full
+
+__global__ __launch_bounds__(kBlock) void k_cliques_wave(const uint32_t *__restrict__ off,
+                                                         const uint32_t *__restrict__ col,
+                                                         const uint32_t *__restrict__ split, int64_t n,
+                                                         const uint32_t *__restrict__ lists, uint32_t count,
+                                                         uint32_t *__restrict__ t_e, ExactAcc *acc)
 {
-    uint32_t m = 0;
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t d = off[u + 1] - off[u] - split[u];
-        m = d > m ? d : m;
+    constexpr int kWaves = kBlock / kWave;
+    __shared__ uint32_t s_key[kWaves][kClSlots];
+    __shared__ uint32_t s_idx[kWaves][kClSlots];
+    __shared__ uint32_t s_row[kWaves][kWave][2];
+    __shared__ uint32_t s_tri[kWaves][kWave];
+    __shared__ unsigned long long s_sum[kWaves];
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    uint32_t *key = s_key[w], *idx = s_idx[w], *tri_u = s_tri[w];
+    uint32_t(*row)[2] = s_row[w];
+    const int grp = lane / 16, sub = lane & 15;
+    unsigned long long k4 = 0, tri = 0;
+    for (uint32_t k = blockIdx.x * kWaves + w; k < count; k += gridDim.x * kWaves) {  // wave-uniform
+        const uint32_t u = list_at(lists, n, kCl64, k);
+        const uint32_t beg = off[u] + split[u], D = off[u + 1] - beg;  // 2 .. 64
+        uint32_t id = 0, vb = 0, ve = 0;
+        if (lane < (int)D) {
+            id = col[beg + lane];
+            vb = off[id] + split[id];
+            ve = off[id + 1];
+        }
+        key[lane] = kNoId;
+        key[lane + kWave] = kNoId;
+        row[lane][0] = row[lane][1] = 0;
+        tri_u[lane] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane < (int)D)
+            for (uint32_t h = hash_mix32(id) & (kClSlots - 1);; h = (h + 1) & (kClSlots - 1))
+                if (atomicCAS(&key[h], kNoId, id) == kNoId) {
+                    idx[h] = (uint32_t)lane;
+                    break;
+                }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (uint32_t i0 = 0; i0 < D; i0 += kWave / 16) {  // wave-uniform
+            const uint32_t i = i0 + grp;
+            const uint32_t b0 = __shfl(vb, (int)(i & 63u), kWave), e0 = __shfl(ve, (int)(i & 63u), kWave);
+            const uint32_t b = i < D ? b0 : 0u, e = i < D ? e0 : 0u;
+            for (uint32_t p = b + sub; p < e; p += 16) {
+                const uint32_t x = col[p];
+                uint32_t h = hash_mix32(x) & (kClSlots - 1), kk;
+                while ((kk = key[h]) != x && kk != kNoId) h = (h + 1) & (kClSlots - 1);
+                if (kk == x) {  // the triangle {u, ids[i], x}; x's index is above i
+                    const uint32_t j = idx[h];
+                    atomicOr(&row[i][j >> 5], 1u << (j & 31));
+                    ++tri;
+                    atomicAdd(&t_e[p], 1u);
+                    atomicAdd(&tri_u[i], 1u);
+                    atomicAdd(&tri_u[j], 1u);
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (tri_u[lane]) atomicAdd(&t_e[beg + lane], tri_u[lane]);  // 0 from D on
+        const uint32_t r0 = row[lane][0], r1 = row[lane][1];
+        uint64_t bits = (uint64_t)r0 | ((uint64_t)r1 << 32);
+        while (bits) {
+            const int j = __builtin_ctzll(bits);
+            bits &= bits - 1;
+            k4 += (unsigned long long)(__popc(r0 & row[j][0]) + __popc(r1 & row[j][1]));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const uint32_t x = __shfl_xor(m, o, kWave);
-        m = x > m ? x : m;
-    }
-    if (lane_id() == 0 && m) atomicMax(out, m);
+    block_add<kBlock>(k4, s_sum, &acc->k4);
+    block_add<kBlock>(tri, s_sum, &acc->tri);
 }
 
 // Sums over forward slots: 2 N_3 = sum t_e (d_u + d_v - 4), N_5 = sum C(t_e, 2)
@@ -265,10 +429,10 @@ __global__ __launch_bounds__(kBlock) void k_edge_sums(const uint32_t *__restrict
     unsigned __int128 n3 = 0, n5 = 0;
     for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < slots;
          s += (int64_t)gridDim.x * blockDim.x) {
-        const SlotRec e = rec[s];
-        const uint32_t u = e.row, v = e.col;
         const uint64_t t = t_e[s];
-        if (v <= u || t == 0) continue;
+        if (t == 0) continue;  // and so at every backward slot
+        const SlotRec e = rec[s];
+        const uint32_t u = e.row;
         const uint64_t du = (uint64_t)(off[u + 1] - off[u]), dv = e.cdeg;
         n3 += (unsigned __int128)t * (du + dv - 4);  // t > 0 means both degrees >= 2
         n5 += (unsigned __int128)(t * (t - 1) / 2);
@@ -283,91 +447,152 @@ __global__ __launch_bounds__(kBlock) void k_edge_sums(const uint32_t *__restrict
 
 // 4-cycles by the highest vertex x.  For each lower neighbour w of x and
 // each lower neighbour y of w below x, the pair (x, y) gains a wedge; a pair
-// with c wedges closes C(c, 2) 4-cycles at x.  Counted per x either in an LDS
-// hash of the touched y (below) or in a counter array of n words per block.
-
-constexpr int kC4Hash = 4096;  // LDS slots of the per-x wedge count table
+// with c wedges closes C(c, 2) 4-cycles at x.  Counted per x in an LDS
+// open-addressing table of the touched y (the classes whose S bounds the
+// distinct y at 3/4 of it), or range of ids by range of ids (below).
 constexpr uint32_t kC4Empty = 0xFFFFFFFFu;
 
-// Vertices x in [0, x_end), one per block at a time, their wedge endpoints
-// counted in an LDS open-addressing table.  An x with more than 3/4 of the
-// table's slots in distinct endpoints is left to the global-array kernel
-// (appended to `spill`).
-__global__ __launch_bounds__(kBlock) void k_four_cycles_lds(const uint32_t *__restrict__ off,
-                                                            const uint32_t *__restrict__ col,
-                                                            const uint32_t *__restrict__ split, int64_t x_end,
-                                                            uint32_t *__restrict__ spill, uint32_t *n_spill,
-                                                            ExactAcc *acc)
+template <uint32_t SLOTS>
+__device__ __forceinline__ void wedge_add(uint32_t *keys, uint32_t *cnts, uint32_t y)
 {
-    __shared__ uint32_t keys[kC4Hash];
-    __shared__ uint32_t cnts[kC4Hash];
-    __shared__ uint32_t touched[kC4Hash];
-    __shared__ uint32_t s_nt, s_fail;
-    const int w_id = threadIdx.x / kWave, lane = lane_id(), nw = kBlock / kWave;
-    for (int i = threadIdx.x; i < kC4Hash; i += kBlock) {
-        keys[i] = kC4Empty;
-        cnts[i] = 0;
-    }
-    unsigned __int128 n4 = 0;
-    for (int64_t x = blockIdx.x; x < x_end; x += gridDim.x) {
-        const uint32_t lo_begin = off[x], lo_end = off[x] + split[x];
-        if (lo_end - lo_begin < 2) continue;  // two wedges at least (block-uniform)
-        if (threadIdx.x == 0) {
-            s_nt = 0;
-            s_fail = 0;
+    for (uint32_t h = hash_mix32(y) & (SLOTS - 1);; h = (h + 1) & (SLOTS - 1)) {
+        uint32_t k = keys[h];
+        if (k == kC4Empty) k = atomicCAS(&keys[h], kC4Empty, y);
+        if (k == kC4Empty || k == y) {
+            atomicAdd(&cnts[h], 1u);
+            return;
         }
-        __syncthreads();
-        for (uint32_t p = lo_begin + w_id; p < lo_end && !s_fail; p += nw) {
-            const uint32_t w = col[p];  // w < x
-            const uint32_t r0 = off[w], r1 = off[w + 1];
-            for (uint32_t q = r0 + lane; q < r1; q += kWave) {
+    }
+}
+
+// A wave per vertex, S <= kC4WaveMax: the rows of 64 lower neighbours at a
+// time are walked as one list (an entry's row by a search in their prefix
+// lengths), so that short rows leave no lane idle.
+__global__ __launch_bounds__(kBlock) void k_c4_wave(const uint32_t *__restrict__ off, const uint32_t *__restrict__ col,
+                                                    const uint32_t *__restrict__ split, int64_t n,
+                                                    const uint32_t *__restrict__ lists, uint32_t count, ExactAcc *acc)
+{
+    constexpr int kWaves = kBlock / kWave;
+    constexpr uint32_t kSlots = 512;
+    __shared__ uint32_t s_key[kWaves][kSlots];
+    __shared__ uint32_t s_cnt[kWaves][kSlots];
+    __shared__ uint32_t s_pre[kWaves][kWave];  // entries before the neighbour's row
+    __shared__ uint32_t s_at[kWaves][kWave];   // its first slot less those
+    __shared__ unsigned long long s_sum[kWaves];
+    const int w_id = threadIdx.x / kWave, lane = lane_id();
+    uint32_t *keys = s_key[w_id], *cnts = s_cnt[w_id], *pre = s_pre[w_id], *at = s_at[w_id];
+#pragma unroll
+    for (int q = 0; q < (int)kSlots / kWave; ++q) {
+        keys[q * kWave + lane] = kC4Empty;
+        cnts[q * kWave + lane] = 0;
+    }
+    unsigned long long n4 = 0;
+    for (uint32_t i = blockIdx.x * kWaves + w_id; i < count; i += gridDim.x * kWaves) {  // wave-uniform
+        const uint32_t x = list_at(lists, n, kC4Wave, i);
+        const uint32_t lo = off[x], D = split[x];
+        for (uint32_t base = 0; base < D; base += kWave) {
+            const uint32_t j = base + lane;
+            uint32_t r0 = 0, len = 0;
+            if (j < D) {
+                const uint32_t w = col[lo + j];
+                r0 = off[w];
+                len = off[w + 1] - r0;
+            }
+            uint32_t incl = len;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t o = __shfl_up(incl, d, kWave);
+                if (lane >= d) incl += o;
+            }
+            const uint32_t total = __shfl(incl, kWave - 1, kWave);
+            pre[lane] = incl - len;
+            at[lane] = r0 - (incl - len);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (uint32_t e = lane; e < total; e += kWave) {
+                uint32_t k = 0;  // the last neighbour with pre[k] <= e (no row is empty)
+#pragma unroll
+                for (uint32_t step = kWave / 2; step > 0; step >>= 1)
+                    if (pre[k + step] <= e) k += step;
+                const uint32_t y = col[at[k] + e];
+                if (y < x) wedge_add<kSlots>(keys, cnts, y);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+#pragma unroll
+        for (int q = 0; q < (int)kSlots / kWave; ++q) {
+            const uint64_t c = cnts[q * kWave + lane];
+            if (c == 0) continue;
+            n4 += c * (c - 1) / 2;
+            keys[q * kWave + lane] = kC4Empty;
+            cnts[q * kWave + lane] = 0;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    n4 = wave_sum_u64(n4);
+    __syncthreads();
+    if (lane == 0) s_sum[w_id] = n4;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned __int128 t = 0;
+        for (int q = 0; q < kWaves; ++q) t += s_sum[q];
+        if (t) add128(&acc->n4_lo, &acc->n4_hi, t);
+    }
+}
+
+// A block per vertex, 16 lanes walking each lower neighbour's row: classes of
+// S <= 3/4 SLOTS.  (A thread's sum stays below 2^64: a vertex adds at most
+// C(S, 2) < 2^27.)
+template <int THREADS, uint32_t SLOTS>
+__global__ __launch_bounds__(THREADS) void k_c4_block(const uint32_t *__restrict__ off,
+                                                      const uint32_t *__restrict__ col,
+                                                      const uint32_t *__restrict__ split, int64_t n,
+                                                      const uint32_t *__restrict__ lists, int cls, uint32_t count,
+                                                      ExactAcc *acc)
+{
+    __shared__ uint32_t keys[SLOTS];
+    __shared__ uint32_t cnts[SLOTS];
+    __shared__ unsigned long long s_sum[THREADS / kWave];
+    const int grp = threadIdx.x / 16, sub = threadIdx.x & 15;
+    for (uint32_t h = threadIdx.x; h < SLOTS; h += THREADS) {
+        keys[h] = kC4Empty;
+        cnts[h] = 0;
+    }
+    __syncthreads();
+    unsigned long long n4 = 0;
+    for (uint32_t i = blockIdx.x; i < count; i += gridDim.x) {  // block-uniform
+        const uint32_t x = list_at(lists, n, cls, i);
+        const uint32_t lo = off[x], D = split[x];
+        for (uint32_t j = grp; j < D; j += THREADS / 16) {
+            const uint32_t w = col[lo + j], r1 = off[w + 1];
+            for (uint32_t q = off[w] + sub; q < r1; q += 16) {
                 const uint32_t y = col[q];
-                if (y >= (uint32_t)x) break;  // rows ascending: the rest are higher too
-                uint32_t h = hash_mix32(y) & (kC4Hash - 1);
-                for (int t = 0; t < kC4Hash; ++t) {
-                    const uint32_t k = keys[h];
-                    if (k == y) {
-                        atomicAdd(&cnts[h], 1u);
-                        break;
-                    }
-                    if (k == kC4Empty) {
-                        const uint32_t old = atomicCAS(&keys[h], kC4Empty, y);
-                        if (old == kC4Empty) {
-                            atomicAdd(&cnts[h], 1u);
-                            const uint32_t nt = atomicAdd(&s_nt, 1u);
-                            touched[nt] = h;
-                            if (nt + 1 > kC4Hash * 3 / 4) s_fail = 1;
-                            break;
-                        }
-                        if (old == y) {
-                            atomicAdd(&cnts[h], 1u);
-                            break;
-                        }
-                    }
-                    h = (h + 1) & (kC4Hash - 1);
-                }
+                if (y >= x) break;  // rows ascend: the rest are higher too
+                wedge_add<SLOTS>(keys, cnts, y);
             }
         }
         __syncthreads();
-        const uint32_t nt = s_nt < (uint32_t)kC4Hash ? s_nt : (uint32_t)kC4Hash;
-        const bool fail = s_fail != 0;
-        for (uint32_t i = threadIdx.x; i < nt; i += kBlock) {
-            const uint32_t h = touched[i];
+        for (uint32_t h = threadIdx.x; h < SLOTS; h += THREADS) {
             const uint64_t c = cnts[h];
-            if (!fail) n4 += (unsigned __int128)(c * (c - 1) / 2);
+            if (c == 0) continue;
+            n4 += c * (c - 1) / 2;
             keys[h] = kC4Empty;
             cnts[h] = 0;
         }
-        if (fail && threadIdx.x == 0) spill[atomicAdd(n_spill, 1u)] = (uint32_t)x;
         __syncthreads();  // the table is clear before the next x
     }
-    n4 = block_sum128<kBlock>(n4);
-    if (threadIdx.x == 0 && n4) add128(&acc->n4_lo, &acc->n4_hi, n4);
+    n4 = wave_sum_u64(n4);
+    if (lane_id() == 0) s_sum[threadIdx.x / kWave] = n4;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned __int128 t = 0;
+        for (int q = 0; q < THREADS / kWave; ++q) t += s_sum[q];
+        if (t) add128(&acc->n4_lo, &acc->n4_hi, t);
+    }
 }
 
-// Vertices x = n-1-b for b < n_top (the highest ids, hubs first), then the
-// spilled ones; blocks take the next b from a queue, so the hubs' unequal
-// work spreads over the blocks as it comes.  The opposite vertices y < x are
+// The vertices of the last class (S > kC4BigMax), about the highest ids first;
+// blocks take the next one from a queue, so the hubs' unequal work spreads
+// over the blocks as it comes.  The opposite vertices y < x are
 // counted one range of ids at a time in LDS: kC4Range 32-bit counters, or
 // twice as many 16-bit ones when x has fewer than 2^16 lower neighbours (a
 // pair's count never exceeds them).  Each lower neighbour w of x keeps a
@@ -390,27 +615,25 @@ constexpr uint32_t kC4Inf = 0xFFFFFFFFu;
 __global__ __launch_bounds__(kC4Threads) void k_four_cycles(const uint32_t *__restrict__ off,
                                                             const uint32_t *__restrict__ col,
                                                             const uint32_t *__restrict__ split, int64_t n,
-                                                            int64_t n_top, const uint32_t *__restrict__ spill,
-                                                            const uint32_t *n_spill, uint4 *__restrict__ state_all,
-                                                            uint64_t cap, uint32_t *queue, ExactAcc *acc)
+                                                            const uint32_t *__restrict__ lists, uint32_t total,
+                                                            uint4 *__restrict__ state_all, uint64_t cap,
+                                                            uint32_t *queue, ExactAcc *acc)
 {
-    __shared__ uint32_t cnt[kC4Range];
+    __shared__ __align__(16) uint32_t cnt[kC4Range];
     __shared__ uint32_t longq[kC4LongCap];
     __shared__ uint32_t s_b, s_nlong;
     uint4 *state = state_all + (uint64_t)blockIdx.x * cap;
     const int tid = threadIdx.x, w_id = tid / kWave, lane = lane_id(), nw = kC4Threads / kWave;
-    const int64_t total = n_top + (int64_t)*n_spill;
     for (uint32_t i = tid; i < kC4Range; i += kC4Threads) cnt[i] = 0;
     unsigned __int128 n4 = 0;
     for (;;) {
         if (tid == 0) s_b = atomicAdd(queue, 1u);
         __syncthreads();
-        const int64_t b = s_b;
+        const uint32_t b = s_b;
         __syncthreads();  // every thread has read s_b before thread 0 writes it again
         if (b >= total) break;  // block-uniform
-        const uint32_t x = b < n_top ? (uint32_t)(n - 1 - b) : spill[b - n_top];
+        const uint32_t x = list_at(lists, n, kC4Ranges, b);
         const uint32_t lo = off[x], D = split[x];  // N-(x) = col[lo, lo + D)
-        if (D < 2) continue;  // fewer than two wedges per pair (block-uniform)
         for (uint32_t i = tid; i < D; i += kC4Threads) {
             const uint32_t w = col[lo + i], c = off[w], e = off[w + 1];
             state[i] = make_uint4(c, e, c < e ? col[c] : kC4Inf, 0u);
@@ -488,36 +711,31 @@ __global__ __launch_bounds__(kC4Threads) void k_four_cycles(const uint32_t *__re
                 if (lane == 0) state[i] = make_uint4(p, st.y, nxt, 0u);
             }
             __syncthreads();
+            // whole 16-byte words of the counters (kC4Range is a multiple of 4
+            // words); a range's sum per thread: below 2^32 words of 2^63
             const uint32_t words = half ? (E - r0 + 1) / 2 : E - r0;
-            for (uint32_t j = tid; j < words; j += kC4Threads) {
-                const uint32_t wv = cnt[j];
-                if (half) {
-                    const uint64_t c0 = wv & 0xFFFFu, c1 = wv >> 16;
-                    n4 += (unsigned __int128)(c0 * (c0 - 1) / 2 + c1 * (c1 - 1) / 2);
-                } else {
-                    const uint64_t c = wv;
-                    n4 += (unsigned __int128)(c * (c - 1) / 2);
+            unsigned __int128 part = 0;
+            for (uint32_t j = tid * 4; j < words; j += kC4Threads * 4) {
+                const uint4 wv = *reinterpret_cast<const uint4 *>(cnt + j);
+                if ((wv.x | wv.y | wv.z | wv.w) == 0) continue;
+                const uint32_t v4[4] = {wv.x, wv.y, wv.z, wv.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (half) {  // two products below 2^31
+                        const uint32_t c0 = v4[q] & 0xFFFFu, c1 = v4[q] >> 16;
+                        part += (uint64_t)(c0 * (c0 - 1) / 2) + (uint64_t)(c1 * (c1 - 1) / 2);
+                    } else {
+                        const uint64_t c = v4[q];
+                        part += c * (c - 1) / 2;
+                    }
                 }
-                cnt[j] = 0;
+                *reinterpret_cast<uint4 *>(cnt + j) = make_uint4(0u, 0u, 0u, 0u);
             }
+            n4 += part;
         }
     }
     n4 = wave_sum128(n4);
     if (lane == 0 && n4) add128(&acc->n4_lo, &acc->n4_hi, n4);
-}
-
-// first vertex with degree above `bound` (degrees ascend)
-__global__ void k_first_above(const uint32_t *__restrict__ deg, int64_t n, uint32_t bound, int64_t *out)
-{
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (deg[mid] > bound)
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    *out = lo;
 }
 
 }  // namespace
@@ -537,44 +755,50 @@ pm_status exact_counts(const pm_graph *g, pm_exact *out, hipStream_t s)
     PM_TRY(fill_async<unsigned char>((unsigned char *)acc, 0, (int64_t)sizeof(ExactAcc), s));
     ProfScope prof_total("exact_total", s);
     if (slots > 0) {
-        uint32_t *split = nullptr, *t_e = nullptr;
+        uint32_t *split = nullptr, *t_e = nullptr, *lists = nullptr;
+        ExactLists *L = nullptr, hl;
         PM_TRY(tmp.get(&split, (size_t)n));
         PM_TRY(tmp.get(&t_e, (size_t)slots));
+        PM_TRY(tmp.get(&lists, (size_t)n * (kExactClasses / 2)));
+        PM_TRY(tmp.get(&L, 1));
+        PM_TRY(fill_async<uint32_t>((uint32_t *)L, 0u, sizeof(ExactLists) / 4, s));
+        {
+            ProfScope prof("exact.classify", s);
+            hipLaunchKernelGGL(k_classify, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, g->off,
+                               g->col, n, split, lists, L);
+            PM_HIP(hipGetLastError());
+        }
+        PM_HIP(hipMemcpyAsync(&hl, L, sizeof(hl), hipMemcpyDeviceToHost, s));
         PM_TRY(fill_async<uint32_t>(t_e, 0u, slots, s));
-        hipLaunchKernelGGL(k_split, dim3(grid_for(n, kBlock, 1 << 22)), dim3(kBlock), 0, s, g->off, g->col, n, split);
+        PM_HIP(hipStreamSynchronize(s));
+        const unsigned cus = (unsigned)sampler_cu_count(g->device);
+        const auto blocks_for = [&](int c, unsigned per_block, unsigned cap) {
+            return dim3(std::min<unsigned>((hl.count[c].n + per_block - 1) / per_block, cap));
+        };
         {
             // triangles (with t_e) and 4-cliques by forward degree class:
-            // rows in LDS up to 1024 members, in a global slice per block
-            // above; vertices with fewer than two forward neighbours close
-            // neither
+            // rows in LDS up to 1024 members, in a global slice per block above
             ProfScope prof("exact.triangles_cliques", s);
-            uint32_t *dmax_d = nullptr;
-            PM_TRY(tmp.get(&dmax_d, 1));
-            PM_TRY(fill_async<uint32_t>(dmax_d, 0u, 1, s));
-            hipLaunchKernelGGL(k_dplus_max, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, g->off, split, n,
-                               dmax_d);
-            uint32_t dmax = 0;
-            PM_HIP(hipMemcpyAsync(&dmax, dmax_d, sizeof(dmax), hipMemcpyDeviceToHost, s));
-            PM_HIP(hipStreamSynchronize(s));
-            const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(n, 8192));
-            {
+            if (hl.count[kCl64].n) {
                 ProfScope pc("exact.cliques.64", s);
-                hipLaunchKernelGGL((k_cliques<2, false, kBlock>), dim3(grid), dim3(kBlock), 0, s, g->off, g->col, split, n,
-                                   1u, 64u, nullptr, 0u, t_e, acc);
+                hipLaunchKernelGGL(k_cliques_wave, blocks_for(kCl64, kBlock / kWave, cus * 8), dim3(kBlock), 0, s,
+                                   g->off, g->col, split, n, lists, hl.count[kCl64].n, t_e, acc);
             }
-            {
+            if (hl.count[kCl256].n) {
                 ProfScope pc("exact.cliques.256", s);
-                hipLaunchKernelGGL((k_cliques<8, false, kBlock>), dim3(grid), dim3(kBlock), 0, s, g->off, g->col, split, n,
-                                   64u, 256u, nullptr, 0u, t_e, acc);
+                hipLaunchKernelGGL((k_cliques<8, false, kBlock>), blocks_for(kCl256, 1, cus * 8), dim3(kBlock), 0, s,
+                                   g->off, g->col, split, n, lists, kCl256, hl.count[kCl256].n, 256u, nullptr, 0u,
+                                   t_e, acc);
             }
-            {
+            if (hl.count[kCl1024].n) {
                 ProfScope pc("exact.cliques.1024", s);
-                hipLaunchKernelGGL((k_cliques<32, false, 1024>), dim3(grid), dim3(1024), 0, s, g->off, g->col, split, n,
-                                   256u, 1024u, nullptr, 0u, t_e, acc);
+                hipLaunchKernelGGL((k_cliques<32, false, 1024>), blocks_for(kCl1024, 1, 8192), dim3(1024), 0, s,
+                                   g->off, g->col, split, n, lists, kCl1024, hl.count[kCl1024].n, 1024u, nullptr, 0u,
+                                   t_e, acc);
             }
-            if (dmax > 1024) {
+            if (hl.count[kClMore].n) {
                 ProfScope pc("exact.cliques.global", s);
-                const uint32_t wd = (dmax + 31) / 32;
+                const uint32_t dmax = hl.dmax.n, wd = (dmax + 31) / 32;
                 const uint64_t slice = ((uint64_t)dmax * wd + 2ull * dmax) * sizeof(uint32_t);
                 // blocks with a slice each, at most 1 GiB of slices
                 const unsigned gb = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(256, (1ull << 30) / slice));
@@ -585,43 +809,47 @@ pm_status exact_counts(const pm_graph *g, pm_exact *out, hipStream_t s)
                 while (gslots < 2 * dmax) gslots <<= 1;
                 const size_t dyn = (2ull * dmax + gslots) * sizeof(uint32_t) + gslots * sizeof(uint16_t);
                 const bool in_lds = dmax < 65536 && dyn <= (64u << 10);
-                hipLaunchKernelGGL((k_cliques<1, true, 1024>), dim3(gb), dim3(1024), in_lds ? dyn : 0, s, g->off, g->col,
-                                   split, n, 1024u, dmax, scr, in_lds ? gslots : 0u, t_e, acc);
+                hipLaunchKernelGGL((k_cliques<1, true, 1024>), blocks_for(kClMore, 1, gb), dim3(1024),
+                                   in_lds ? dyn : 0, s, g->off, g->col, split, n, lists, kClMore,
+                                   hl.count[kClMore].n, dmax, scr, in_lds ? gslots : 0u, t_e, acc);
             }
-            hipLaunchKernelGGL(k_edge_sums, dim3(grid_for(slots, kBlock, 4096)), dim3(kBlock), 0, s, g->off, g->rec,
+            hipLaunchKernelGGL(k_edge_sums, dim3(grid_for(slots, kBlock, 1024)), dim3(kBlock), 0, s, g->off, g->rec,
                                t_e, slots, acc);
             PM_HIP(hipGetLastError());
             tmp.release(t_e);
         }
-        // 4-cycles: vertices of degree at most kC4LdsDegree in LDS tables,
-        // the rest (and any whose table fills) range by range in LDS
-        constexpr uint32_t kC4LdsDegree = 1024;
+        // 4-cycles: by the class's table, or range by range in LDS
         ProfScope prof("exact.four_cycles", s);
-        int64_t *xb_d = nullptr;
-        uint32_t *spill = nullptr, *n_spill = nullptr;
-        PM_TRY(tmp.get(&xb_d, 1));
-        PM_TRY(tmp.get(&n_spill, 1));
-        hipLaunchKernelGGL(k_first_above, dim3(1), dim3(1), 0, s, g->deg, n, kC4LdsDegree, xb_d);
-        PM_TRY(fill_async<uint32_t>(n_spill, 0u, 1, s));
-        int64_t x_big = 0;
-        PM_HIP(hipMemcpyAsync(&x_big, xb_d, sizeof(x_big), hipMemcpyDeviceToHost, s));
-        PM_HIP(hipStreamSynchronize(s));
-        PM_TRY(tmp.get(&spill, (size_t)std::max<int64_t>(x_big, 1)));
-        if (x_big > 0)
-            hipLaunchKernelGGL(k_four_cycles_lds, dim3((unsigned)std::min<int64_t>(x_big, 16384)), dim3(kBlock), 0, s,
-                               g->off, g->col, split, x_big, spill, n_spill, acc);
-        // one cursor state (16 bytes) per lower neighbour of the block's
-        // current vertex: at most dmax, within a 4 GiB budget of blocks
-        const uint64_t cap = (uint64_t)std::max<int64_t>(g->dmax, 1);
-        const int blocks = (int)std::max<uint64_t>(
-            1, std::min<uint64_t>(std::min<uint64_t>(256, (uint64_t)n), (4ull << 30) / (cap * sizeof(uint4))));
-        uint4 *state = nullptr;
-        uint32_t *queue = nullptr;
-        PM_TRY(tmp.get(&state, (size_t)blocks * (size_t)cap));
-        PM_TRY(tmp.get(&queue, 1));
-        PM_TRY(fill_async<uint32_t>(queue, 0u, 1, s));
-        hipLaunchKernelGGL(k_four_cycles, dim3(blocks), dim3(kC4Threads), 0, s, g->off, g->col, split, n, n - x_big,
-                           spill, n_spill, state, cap, queue, acc);
+        if (hl.count[kC4Ranges].n) {
+            ProfScope pc("exact.four_cycles.ranges", s);
+            // one cursor state (16 bytes) per lower neighbour of the block's
+            // current vertex: at most dmax, within a 4 GiB budget of blocks
+            const uint64_t cap = (uint64_t)std::max<int64_t>(g->dmax, 1);
+            const unsigned blocks = (unsigned)std::max<uint64_t>(
+                1, std::min<uint64_t>(std::min<uint64_t>(256, hl.count[kC4Ranges].n), (4ull << 30) / (cap * sizeof(uint4))));
+            uint4 *state = nullptr;
+            uint32_t *queue = nullptr;
+            PM_TRY(tmp.get(&state, (size_t)blocks * (size_t)cap));
+            PM_TRY(tmp.get(&queue, 1));
+            PM_TRY(fill_async<uint32_t>(queue, 0u, 1, s));
+            hipLaunchKernelGGL(k_four_cycles, dim3(blocks), dim3(kC4Threads), 0, s, g->off, g->col, split, n, lists,
+                               hl.count[kC4Ranges].n, state, cap, queue, acc);
+        }
+        if (hl.count[kC4Big].n) {
+            ProfScope pc("exact.four_cycles.16384", s);
+            hipLaunchKernelGGL((k_c4_block<1024, 16384>), blocks_for(kC4Big, 1, cus), dim3(1024), 0, s, g->off, g->col,
+                               split, n, lists, kC4Big, hl.count[kC4Big].n, acc);
+        }
+        if (hl.count[kC4Block].n) {
+            ProfScope pc("exact.four_cycles.4096", s);
+            hipLaunchKernelGGL((k_c4_block<kBlock, 4096>), blocks_for(kC4Block, 1, cus * 4), dim3(kBlock), 0, s, g->off,
+                               g->col, split, n, lists, kC4Block, hl.count[kC4Block].n, acc);
+        }
+        if (hl.count[kC4Wave].n) {
+            ProfScope pc("exact.four_cycles.512", s);
+            hipLaunchKernelGGL(k_c4_wave, blocks_for(kC4Wave, kBlock / kWave, cus * 8), dim3(kBlock), 0, s, g->off,
+                               g->col, split, n, lists, hl.count[kC4Wave].n, acc);
+        }
         PM_HIP(hipGetLastError());
     }
     ExactAcc h;
