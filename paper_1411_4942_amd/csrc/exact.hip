@@ -110,14 +110,22 @@ __device__ __forceinline__ void block_add(unsigned long long v, unsigned long lo
     }
 }
 
+constexpr uint32_t kNoId = 0xFFFFFFFFu;  // not a vertex id (they are below 2^31): an empty member-hash slot
+
 // The vertices by the kernels that handle them.  Triangles and 4-cliques:
 // classes by forward degree D.  4-cycles: classes by S, the sum of the degrees
 // of x's lower neighbours (at least the wedges counted at x), which bounds the
 // distinct ids a table must hold.
-enum : int { kCl64, kCl256, kCl1024, kClMore, kC4Wave, kC4Block, kC4Big, kC4Ranges, kExactClasses };
+enum : int { kCl64, kCl256, kCl1024, kClMore, kC4Wave, kC4Block, kC4Big, kC4Bits, kC4Ranges, kExactClasses };
 constexpr uint32_t kC4WaveMax = 384;    // wedges: tables of 512, 4096 and 16384 slots, at most 3/4 full
 constexpr uint32_t kC4BlockMax = 3072;
 constexpr uint32_t kC4BigMax = 12288;
+// above, where the ranges of k_four_cycles would be many: a bitmap of the ids
+// (spans of kC4Span) and a table of the repeated ones
+constexpr uint32_t kC4BitsMax = 60000;
+constexpr uint32_t kC4BitsFrom = 1u << 18;  // x from here on: 4 ranges of ids or more
+constexpr uint32_t kC4Span = 1u << 20;
+constexpr uint32_t kC4Spans = 4;            // each span walks the rows again
 
 // Counters on lines of their own, and the largest forward degree.
 struct ExactLists {
@@ -129,7 +137,9 @@ struct ExactLists {
 };
 
 // Class c's list lies in array c / 2 of n words: even classes from the front,
-// odd ones from the back (a vertex is in at most one class of each pair).
+// odd ones from the back (a vertex is in at most one class of each pair; the
+// last class has an array of its own, since a vertex of kC4Bits can join it).
+constexpr int kExactArrays = (kExactClasses + 1) / 2;
 __device__ __forceinline__ uint32_t list_at(const uint32_t *__restrict__ lists, int64_t n, int c, uint32_t i)
 {
     const uint32_t *a = lists + (int64_t)(c / 2) * n;
@@ -139,7 +149,7 @@ __device__ __forceinline__ uint32_t list_at(const uint32_t *__restrict__ lists, 
 // split[x] = number of neighbours of x below x (rows ascending), and the
 // lists.  A block takes kBlock vertices, highest ids (the heaviest) first:
 // 16 lanes per vertex find its split and sum its lower neighbours' degrees,
-// highest first, until they pass kC4BigMax; then a thread per vertex appends
+// highest first, until they pass kC4BitsMax; then a thread per vertex appends
 // it, one atomic per class and block.
 constexpr int kClassLanes = 16;
 
@@ -169,13 +179,19 @@ __global__ __launch_bounds__(kBlock) void k_classify(const uint32_t *__restrict_
                     hi = mid;
             }
             sp = lo - a;
-            for (uint32_t k = 0; k < sp && sum <= kC4BigMax; k += kClassLanes) {
-                uint32_t dw = 0;
-                if (k + sub < sp) {
-                    const uint32_t w = col[a + sp - 1 - (k + sub)];
-                    dw = off[w + 1] - off[w];
-                    dw = dw > kC4BigMax ? kC4BigMax + 1 : dw;
+            for (uint32_t k = 0; k < sp && sum <= kC4BitsMax; k += 4 * kClassLanes) {
+                uint32_t w[4], dw = 0;  // four reads in flight
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t i = k + j * kClassLanes + sub;
+                    w[j] = i < sp ? col[a + sp - 1 - i] : kNoId;
                 }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (w[j] != kNoId) {
+                        const uint32_t dj = off[w[j] + 1] - off[w[j]];
+                        dw += dj > kC4BitsMax ? kC4BitsMax + 1 : dj;
+                    }
 #pragma unroll
                 for (int o = kClassLanes / 2; o > 0; o >>= 1) dw += __shfl_xor(dw, o, kClassLanes);
                 sum += dw;
@@ -195,7 +211,12 @@ __global__ __launch_bounds__(kBlock) void k_classify(const uint32_t *__restrict_
         const uint32_t sp = s_split[t], D = s_deg[t] - sp, S = s_sum[t];
         split[x] = sp;
         if (D >= 2) cl = D <= 64 ? kCl64 : D <= 256 ? kCl256 : D <= 1024 ? kCl1024 : kClMore;
-        if (sp >= 2) c4 = S <= kC4WaveMax ? kC4Wave : S <= kC4BlockMax ? kC4Block : S <= kC4BigMax ? kC4Big : kC4Ranges;
+        if (sp >= 2)
+            c4 = S <= kC4WaveMax    ? kC4Wave
+                 : S <= kC4BlockMax ? kC4Block
+                 : S <= kC4BigMax   ? kC4Big
+                 : S <= kC4BitsMax && sp < 4095 && x >= kC4BitsFrom && n <= (int64_t)kC4Spans * kC4Span ? kC4Bits
+                                                                                                        : kC4Ranges;
         if (cl >= 0) icl = atomicAdd(&s_n[cl], 1u);
         if (c4 >= 0) ic4 = atomicAdd(&s_n[c4], 1u);
         if (D >= 2) atomicMax(&s_dmax, D);
@@ -226,8 +247,6 @@ __global__ __launch_bounds__(kBlock) void k_classify(const uint32_t *__restrict_
 // rows, in the block's slice of a global scratch array.  A member is found
 // in an LDS hash of N+(u) (id -> index, at most half full: one or two
 // reads) in the LDS classes, by binary search in the global one.
-constexpr uint32_t kNoId = 0xFFFFFFFFu;  // an empty member-hash slot (vertex ids are below 2^31)
-
 template <int W, bool GLOBAL, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_cliques(const uint32_t *__restrict__ off,
                                                     const uint32_t *__restrict__ col,
@@ -590,40 +609,141 @@ __global__ __launch_bounds__(THREADS) void k_c4_block(const uint32_t *__restrict
     }
 }
 
-// The vertices of the last class (S > kC4BigMax), about the highest ids first;
+// A block per vertex x of more wedges than a table holds, most of them to ids
+// y reached once (a Chung-Lu graph of 1e6 vertices: 45K wedges to 41K ids):
+// a bitmap of one span of ids shows which wedges repeat, and only those are
+// counted, in a small table (id in the span << 12 | repeats; a pair's count
+// is at most D < 4095).  A y of r repeats has r + 1 wedges, C(r + 1, 2)
+// cycles.  A vertex whose table fills joins the last class.
+// With it the vertices of 12288 < S <= 60000 took 0.53 ms on Chung-Lu 1e7
+// edges, range by range (below) 1.7.
+constexpr int kC4BitsThreads = 1024;
+constexpr uint32_t kC4BitsSlots = 6144;
+constexpr uint32_t kC4BitsFull = kC4BitsSlots * 4 / 5;
+
+__global__ __launch_bounds__(kC4BitsThreads) void k_c4_bits(const uint32_t *__restrict__ off,
+                                                            const uint32_t *__restrict__ col,
+                                                            const uint32_t *__restrict__ split, int64_t n,
+                                                            uint32_t *__restrict__ lists, uint32_t count,
+                                                            ExactLists *L, ExactAcc *acc)
+{
+    __shared__ uint4 s_bits4[kC4Span / 128];
+    __shared__ uint32_t s_tab[kC4BitsSlots];
+    __shared__ uint32_t s_used;
+    __shared__ unsigned long long s_sum[kC4BitsThreads / kWave];
+    const int tid = threadIdx.x, grp = tid / 16, sub = tid & 15;
+    for (uint32_t j = tid; j < kC4Span / 128; j += kC4BitsThreads) s_bits4[j] = make_uint4(0u, 0u, 0u, 0u);
+    for (uint32_t j = tid; j < kC4BitsSlots; j += kC4BitsThreads) s_tab[j] = kC4Empty;
+    if (tid == 0) s_used = 0;
+    __syncthreads();
+    unsigned int *const bits = reinterpret_cast<unsigned int *>(s_bits4);
+    // one more repeat of id r0 + o; a full table is noted in s_used
+    const auto repeat = [&](uint32_t o) {
+        uint32_t h = hash_home(o, kC4BitsSlots);
+        for (uint32_t probe = 0; probe < kC4BitsSlots; ++probe) {
+            uint32_t k = s_tab[h];
+            if (k == kC4Empty) {
+                k = atomicCAS(&s_tab[h], kC4Empty, o << 12 | 1u);
+                if (k == kC4Empty) {
+                    atomicAdd(&s_used, 1u);
+                    return;
+                }
+            }
+            if (k >> 12 == o) {
+                atomicAdd(&s_tab[h], 1u);
+                return;
+            }
+            h = h + 1 == kC4BitsSlots ? 0u : h + 1;
+        }
+        atomicAdd(&s_used, kC4BitsSlots);
+    };
+    unsigned long long n4 = 0;
+    for (uint32_t i = blockIdx.x; i < count; i += gridDim.x) {  // block-uniform
+        const uint32_t x = list_at(lists, n, kC4Bits, i);
+        const uint32_t lo = off[x], D = split[x];
+        unsigned long long part = 0;
+        bool full = false;
+        for (uint32_t r0 = 0; r0 < x && !full; r0 += kC4Span) {  // block-uniform
+            const uint32_t E = x - r0 < kC4Span ? x : r0 + kC4Span;
+            for (uint32_t j = grp; j < D; j += kC4BitsThreads / 16) {
+                if (s_used > kC4BitsFull) break;
+                const uint32_t w = col[lo + j], r1 = off[w + 1];
+                for (uint32_t q = off[w] + sub; q < r1; q += 16) {
+                    const uint32_t y = col[q];
+                    if (y >= E) break;  // rows ascend: the rest are higher too
+                    if (y < r0) continue;
+                    const uint32_t o = y - r0, bit = 1u << (o & 31);
+                    if (atomicOr(&bits[o >> 5], bit) & bit) repeat(o);
+                }
+            }
+            __syncthreads();
+            full = s_used > kC4BitsFull;
+            __syncthreads();  // read by all before it is cleared
+            if (tid == 0) s_used = 0;
+            for (uint32_t j = tid; j < kC4BitsSlots; j += kC4BitsThreads) {
+                const uint32_t k = s_tab[j];
+                if (k == kC4Empty) continue;
+                const uint64_t r = k & 4095u;
+                part += r * (r + 1) / 2;
+                s_tab[j] = kC4Empty;
+            }
+            for (uint32_t j = tid; j < kC4Span / 128; j += kC4BitsThreads) s_bits4[j] = make_uint4(0u, 0u, 0u, 0u);
+            __syncthreads();  // clear before the next span
+        }
+        if (!full)
+            n4 += part;
+        else if (tid == 0)
+            lists[(int64_t)(kC4Ranges / 2) * n + atomicAdd(&L->count[kC4Ranges].n, 1u)] = x;
+    }
+    n4 = wave_sum_u64(n4);
+    if (lane_id() == 0) s_sum[tid / kWave] = n4;
+    __syncthreads();
+    if (tid == 0) {
+        unsigned __int128 t = 0;
+        for (int q = 0; q < kC4BitsThreads / kWave; ++q) t += s_sum[q];
+        if (t) add128(&acc->n4_lo, &acc->n4_hi, t);
+    }
+}
+
+// The vertices of the last class, about the highest ids first;
 // blocks take the next one from a queue, so the hubs' unequal work spreads
 // over the blocks as it comes.  The opposite vertices y < x are
 // counted one range of ids at a time in LDS: kC4Range 32-bit counters, or
 // twice as many 16-bit ones when x has fewer than 2^16 lower neighbours (a
 // pair's count never exceeds them).  Each lower neighbour w of x keeps a
 // cursor into its row (rows ascend, so the entries of one range follow
-// those of the range before): per range a lane reads the cursor and the id
-// it points at, and walks the row's segment inside the range only when that
-// id lies in it.  A row is thus read segment by
-// segment, about once over all ranges, instead of one random counter update
-// in global memory per wedge.  Lanes walk up to kC4LaneRun entries of a
-// segment; longer segments go to an LDS queue that whole waves walk 64
-// entries at a time.
+// those of the range before): per range the four lanes that stand for w read
+// the cursor and the id it points at (the next w's while this one is walked),
+// and walk the row's segment inside the range only when that id lies in it,
+// kC4In entries per lane at once.  What bounds it is the latency of those
+// reads with one block's 16 waves per CU (the counters fill its LDS).  A lane
+// per w, 4 entries at once and long segments queued to whole waves, took
+// 2.83 ms on Chung-Lu 1e7 edges (1.5 ms here), 1.30 on R-MAT scale 16 (0.36)
+// and 516 on R-MAT scale 22 (289); 4 or 16 entries per lane measured up to 10%
+// slower.
 constexpr int kC4Threads = 1024;
-constexpr uint32_t kC4Range = 40448;  // LDS counters per range (all of a 160 KB LDS but the words below)
-constexpr uint32_t kC4LongCap = 256;  // queued long segments per range
-constexpr int kC4LaneRun = 16;        // entries a lane walks before queueing the rest of a segment
+constexpr uint32_t kC4Range = 40448;  // LDS counters per range (nearly all of a 160 KB LDS)
+constexpr int kC4Lanes = 4;           // per lower neighbour
+constexpr int kC4In = 8;              // entries of its row that a lane reads at once
 constexpr uint32_t kC4Inf = 0xFFFFFFFFu;
+static_assert(kC4Range % 4 == 0, "the counters are read 16 bytes at a time");
 
 // state[i] of the i-th lower neighbour w of the current x: {cursor into row
 // w, end of row w, id at the cursor (kC4Inf past the end), unused}
 __global__ __launch_bounds__(kC4Threads) void k_four_cycles(const uint32_t *__restrict__ off,
                                                             const uint32_t *__restrict__ col,
                                                             const uint32_t *__restrict__ split, int64_t n,
-                                                            const uint32_t *__restrict__ lists, uint32_t total,
+                                                            const uint32_t *__restrict__ lists,
+                                                            const ExactLists *__restrict__ L,
                                                             uint4 *__restrict__ state_all, uint64_t cap,
                                                             uint32_t *queue, ExactAcc *acc)
 {
     __shared__ __align__(16) uint32_t cnt[kC4Range];
-    __shared__ uint32_t longq[kC4LongCap];
-    __shared__ uint32_t s_b, s_nlong;
+    __shared__ uint32_t s_b;
     uint4 *state = state_all + (uint64_t)blockIdx.x * cap;
-    const int tid = threadIdx.x, w_id = tid / kWave, lane = lane_id(), nw = kC4Threads / kWave;
+    const int tid = threadIdx.x, lane = lane_id();
+    const uint32_t sub = tid & (kC4Lanes - 1);
+    const uint32_t total = L->count[kC4Ranges].n;
     for (uint32_t i = tid; i < kC4Range; i += kC4Threads) cnt[i] = 0;
     unsigned __int128 n4 = 0;
     for (;;) {
@@ -649,66 +769,48 @@ __global__ __launch_bounds__(kC4Threads) void k_four_cycles(const uint32_t *__re
             else
                 atomicAdd(&cnt[o], 1u);
         };
+        __syncthreads();  // the state and the cleared counters are in place
         for (uint32_t r0 = 0; r0 < x; r0 += span) {
             const uint32_t E = x - r0 < span ? x : r0 + span;  // this range: ids [r0, E)
-            if (tid == 0) s_nlong = 0;
-            __syncthreads();  // the state, the cleared counters and s_nlong are in place
-            for (uint32_t i = tid; i < D; i += kC4Threads) {
-                const uint4 st = state[i];
-                if (st.z >= E) continue;  // nothing of row w in this range
-                uint32_t p = st.x, nxt = kC4Inf;
-                const uint32_t end = st.y;
-                bool queued = false, lane_only = false;
-                for (int taken = 0;;) {
-                    uint32_t v[4];
+            uint4 st = make_uint4(0u, 0u, kC4Inf, 0u);
+            uint32_t i = (uint32_t)tid / kC4Lanes;
+            if (i < D) st = state[i];
+            for (; i < D; i += kC4Threads / kC4Lanes) {
+                uint4 ahead = make_uint4(0u, 0u, kC4Inf, 0u);
+                if (i + kC4Threads / kC4Lanes < D) ahead = state[i + kC4Threads / kC4Lanes];
+                if (st.z < E) {
+                    uint32_t p = st.x, nxt, in;
+                    do {
+                        uint32_t v[kC4In];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = p + j < end ? col[p + j] : kC4Inf;
-                    int j = 0;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (j < q || v[q] >= E) continue;  // stop at the first id past the range
-                        bump(v[q], r0);
-                        j = q + 1;
-                    }
-                    p += j;
-                    if (j < 4) {
-                        nxt = v[j];  // the first id >= E, or kC4Inf past the row's end
-                        break;
-                    }
-                    taken += 4;
-                    if (!lane_only && taken >= kC4LaneRun) {
-                        const uint32_t q = atomicAdd(&s_nlong, 1u);
-                        if (q < kC4LongCap) {
-                            longq[q] = i;
-                            queued = true;
-                            break;
+                        for (int j = 0; j < kC4In; ++j) {
+                            const uint32_t q = p + j * kC4Lanes + sub;
+                            v[j] = q < st.y ? col[q] : kC4Inf;
                         }
-                        lane_only = true;  // the queue is full: this lane walks on
-                    }
+                        // the entries in the range are the first ones read
+                        // (rows ascend), the smallest other one is the next
+                        in = 0;
+                        nxt = kC4Inf;
+#pragma unroll
+                        for (int j = 0; j < kC4In; ++j) {
+                            if (v[j] < E) {
+                                bump(v[j], r0);
+                                ++in;
+                            } else {
+                                nxt = v[j] < nxt ? v[j] : nxt;
+                            }
+                        }
+#pragma unroll
+                        for (int o = kC4Lanes / 2; o > 0; o >>= 1) {
+                            in += __shfl_xor(in, o, kC4Lanes);
+                            const uint32_t other = __shfl_xor(nxt, o, kC4Lanes);
+                            nxt = other < nxt ? other : nxt;
+                        }
+                        p += in;
+                    } while (in == kC4Lanes * kC4In);  // the same in the four lanes
+                    if (sub == 0) state[i] = make_uint4(p, st.y, nxt, 0u);
                 }
-                state[i] = make_uint4(p, end, queued ? 0u : nxt, 0u);
-            }
-            __syncthreads();
-            // the long segments, a wave each, 64 entries per step (a prefix of
-            // each step's ids lies in the range: rows ascend)
-            const uint32_t nl = s_nlong < kC4LongCap ? s_nlong : kC4LongCap;
-            for (uint32_t q = w_id; q < nl; q += nw) {  // wave-uniform
-                const uint32_t i = longq[q];
-                const uint4 st = state[i];
-                uint32_t p = st.x, nxt = kC4Inf;
-                for (;;) {
-                    const uint32_t idx = p + lane;
-                    const uint32_t y = idx < st.y ? col[idx] : kC4Inf;
-                    const bool in = y < E;
-                    if (in) bump(y, r0);
-                    const uint32_t c = (uint32_t)__popcll(__ballot(in));
-                    p += c;
-                    if (c < (uint32_t)kWave) {
-                        nxt = __shfl(y, (int)c, kWave);
-                        break;
-                    }
-                }
-                if (lane == 0) state[i] = make_uint4(p, st.y, nxt, 0u);
+                st = ahead;
             }
             __syncthreads();
             // whole 16-byte words of the counters (kC4Range is a multiple of 4
@@ -732,6 +834,9 @@ __global__ __launch_bounds__(kC4Threads) void k_four_cycles(const uint32_t *__re
                 *reinterpret_cast<uint4 *>(cnt + j) = make_uint4(0u, 0u, 0u, 0u);
             }
             n4 += part;
+            // at the loop's end: at its head the compiler leaves out the wait
+            // for the stores above
+            __syncthreads();
         }
     }
     n4 = wave_sum128(n4);
@@ -759,7 +864,7 @@ pm_status exact_counts(const pm_graph *g, pm_exact *out, hipStream_t s)
         ExactLists *L = nullptr, hl;
         PM_TRY(tmp.get(&split, (size_t)n));
         PM_TRY(tmp.get(&t_e, (size_t)slots));
-        PM_TRY(tmp.get(&lists, (size_t)n * (kExactClasses / 2)));
+        PM_TRY(tmp.get(&lists, (size_t)n * kExactArrays));
         PM_TRY(tmp.get(&L, 1));
         PM_TRY(fill_async<uint32_t>((uint32_t *)L, 0u, sizeof(ExactLists) / 4, s));
         {
@@ -820,20 +925,26 @@ pm_status exact_counts(const pm_graph *g, pm_exact *out, hipStream_t s)
         }
         // 4-cycles: by the class's table, or range by range in LDS
         ProfScope prof("exact.four_cycles", s);
-        if (hl.count[kC4Ranges].n) {
+        if (hl.count[kC4Bits].n) {
+            ProfScope pc("exact.four_cycles.bits", s);
+            hipLaunchKernelGGL(k_c4_bits, blocks_for(kC4Bits, 1, cus), dim3(kC4BitsThreads), 0, s, g->off, g->col,
+                               split, n, lists, hl.count[kC4Bits].n, L, acc);
+        }
+        if (hl.count[kC4Ranges].n + hl.count[kC4Bits].n) {  // and those whose repeats filled their table
             ProfScope pc("exact.four_cycles.ranges", s);
             // one cursor state (16 bytes) per lower neighbour of the block's
             // current vertex: at most dmax, within a 4 GiB budget of blocks
             const uint64_t cap = (uint64_t)std::max<int64_t>(g->dmax, 1);
             const unsigned blocks = (unsigned)std::max<uint64_t>(
-                1, std::min<uint64_t>(std::min<uint64_t>(256, hl.count[kC4Ranges].n), (4ull << 30) / (cap * sizeof(uint4))));
+                1, std::min<uint64_t>(std::min<uint64_t>(256, (uint64_t)hl.count[kC4Ranges].n + hl.count[kC4Bits].n),
+                                      (4ull << 30) / (cap * sizeof(uint4))));
             uint4 *state = nullptr;
             uint32_t *queue = nullptr;
             PM_TRY(tmp.get(&state, (size_t)blocks * (size_t)cap));
             PM_TRY(tmp.get(&queue, 1));
             PM_TRY(fill_async<uint32_t>(queue, 0u, 1, s));
-            hipLaunchKernelGGL(k_four_cycles, dim3(blocks), dim3(kC4Threads), 0, s, g->off, g->col, split, n, lists,
-                               hl.count[kC4Ranges].n, state, cap, queue, acc);
+            hipLaunchKernelGGL(k_four_cycles, dim3(blocks), dim3(kC4Threads), 0, s, g->off, g->col, split, n, lists, L,
+                               state, cap, queue, acc);
         }
         if (hl.count[kC4Big].n) {
             ProfScope pc("exact.four_cycles.16384", s);

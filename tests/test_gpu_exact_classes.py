@@ -53,3 +53,31 @@ def test_tree_fills_tables(q, k):
     # 3-paths: over edges (root, hub) and (hub, leaf), (d_u - 1)(d_v - 1)
     assert e["C"][2] == q * (q - 1) * (k - 1)
     assert e["C"][3:] == [0, 0, 0, 0] and e["triangles"] == 0
+
+
+# vertices above id 2^18 (the ids below are isolated) with more wedges than a
+# table holds: counted with a bitmap, or range by range when too many repeat.
+# 2^20 + 5000: the ids of a span's edge lie among the counted ones.
+@pytest.mark.parametrize("n", [300000, (1 << 20) + 5000, 2200000])
+@pytest.mark.parametrize("kind", ["few repeats", "hubs", "many repeats"])
+def test_wedges_above_the_tables(n, kind):
+    print("[case] exact bits", n, kind, flush=True)
+    if kind == "hubs":  # K_{6,2500}
+        off, col = synth.complete_bipartite(6, 2500)
+        u, v = synth.edges_of(off, col)
+        c4 = comb(6, 2) * comb(2500, 2)
+    elif kind == "few repeats":  # a root over 200 hubs of 150 leaves, and 7 leaves shared by two hubs
+        hubs = np.arange(1, 201)
+        leaves = 201 + np.arange(200 * 150)
+        u = np.concatenate([np.zeros(200, np.int64), np.repeat(hubs, 150), np.full(7, 2)])
+        v = np.concatenate([hubs, leaves, leaves[:7]])
+        c4 = comb(7, 2) + 7  # pairs of shared leaves, and a shared leaf with the root
+    else:  # x over two sets of 4, each fully joined to 4000 others; x's own 4000 leaves put it on top
+        a, b = np.arange(1, 9), 9 + np.arange(8000)
+        leaves = 8009 + np.arange(4000)
+        u = np.concatenate([np.zeros(8, np.int64), np.zeros(4000, np.int64), np.repeat(a[:4], 4000), np.repeat(a[4:], 4000)])
+        v = np.concatenate([a, leaves, np.tile(b[:4000], 4), np.tile(b[4000:], 4)])
+        c4 = 2 * comb(4, 2) * comb(4001, 2)
+    e = _exact(*synth.csr_from_edges(n, u, v))
+    assert e["N"][4] == c4
+    assert e["triangles"] == 0
