@@ -38,18 +38,65 @@ double kl(double a, double b)
     return t1 + t2;
 }
 
-// root of D(alpha, p) = target for p in [lo, hi], D monotone there
-double bisect(double alpha, double target, double lo, double hi, bool increasing)
+// The roots p < alpha < p of D(alpha, p) = target, by Newton's method.
+// Bisection took 53 to 200 evaluations of D a root, 37 us a result of eight
+// intervals (one host core); from the starts below it is two to six, 3.5 us.
+//
+// Near alpha the unknown is d = p - alpha, and
+//   D = -alpha log1p(d / alpha) - beta log1p(-d / beta),   beta = 1 - alpha,
+// whose rounding leaves p accurate to its last bits (bisecting the two
+// logarithms' difference loses digits where D is small).  D is convex, and a
+// step out of the bracket of known signs is replaced by its middle.
+double near_root(double alpha, double beta, double target, double d, double lo, double hi, bool increasing)
 {
-    for (int it = 0; it < 200 && hi - lo > 1e-16; ++it) {
-        double mid = 0.5 * (lo + hi);
-        double f = kl(alpha, mid) - target;
+    for (int it = 0; it < 200; ++it) {
+        const double f = -alpha * std::log1p(d / alpha) - beta * std::log1p(-d / beta) - target;
         if ((f > 0) == increasing)
-            hi = mid;
+            hi = d;
         else
-            lo = mid;
+            lo = d;
+        const double p = alpha + d;
+        double next = d - f * p * (beta - d) / d;  // D' = d / (p (1 - p))
+        if (!(next > lo && next < hi)) next = 0.5 * (lo + hi);
+        const double step = std::fabs(next - d);
+        if (next == lo || next == hi) break;  // the bracket is two neighbours
+        d = next;
+        if (step <= 1e-16 * p) break;
     }
-    return 0.5 * (lo + hi);
+    return alpha + d;
+}
+
+// The lower root far from alpha: the unknown is ln p, in which D is convex
+// and nearly straight; D >= alpha ln(alpha / p) - (alpha - p) puts the start
+// at or below the root, from where the steps only rise.
+double far_lower_root(double alpha, double beta, double target)
+{
+    double p = std::fmax(alpha * std::exp(-1.0 - target / alpha), 5e-324);
+    for (int it = 0; it < 200; ++it) {
+        const double f = -alpha * std::log(p / alpha) - beta * std::log1p((alpha - p) / beta) - target;
+        const double next = p * std::exp(f * (1.0 - p) / (alpha - p));
+        if (!(next < alpha) || !(next > 0.0)) break;
+        const double step = std::fabs(next - p);
+        p = next;
+        if (step <= 1e-16 * p) break;
+    }
+    return p;
+}
+
+double lower_root(double alpha, double beta, double target)
+{
+    const double s = std::sqrt(2.0 * alpha * beta * target);
+    const double d = -s + (beta - alpha) * target * (2.0 / 3.0);  // D to third order in d
+    if (d > -0.5 * alpha && d < 0.0) return near_root(alpha, beta, target, d, -alpha, 0.0, false);
+    return far_lower_root(alpha, beta, target);
+}
+
+double upper_root(double alpha, double beta, double target)
+{
+    const double s = std::sqrt(2.0 * alpha * beta * target);
+    const double d = s + (beta - alpha) * target * (2.0 / 3.0);
+    if (d < 0.5 * beta && d > 0.0) return near_root(alpha, beta, target, d, 0.0, beta, true);
+    return 1.0 - far_lower_root(beta, alpha, target);  // D(alpha, p) = D(beta, 1 - p)
 }
 
 }  // namespace
@@ -60,7 +107,7 @@ pm_status chernoff_interval(uint64_t count, uint64_t k, double delta, double *p_
         set_error("chernoff_interval: need k > 0, count <= k, delta in (0,1)");
         return PM_EINVAL;
     }
-    const double target = std::log(1.0 / delta) / (double)k;
+    const double target = -std::log(delta) / (double)k;  // (1 / delta rounds: digits lost near delta = 1)
     if (count == 0) {
         *p_lo = 0.0;
         *p_hi = 1.0 - std::pow(delta, 1.0 / (double)k);
@@ -71,9 +118,12 @@ pm_status chernoff_interval(uint64_t count, uint64_t k, double delta, double *p_
         *p_hi = 1.0;
         return PM_OK;
     }
-    const double alpha = (double)count / (double)k;
-    *p_lo = kl(alpha, 5e-324) <= target ? 0.0 : bisect(alpha, target, 0.0, alpha, false);
-    *p_hi = kl(alpha, std::nextafter(1.0, 0.0)) <= target ? 1.0 : bisect(alpha, target, alpha, 1.0, true);
+    const double alpha = (double)count / (double)k, beta = (double)(k - count) / (double)k;
+    // (the bounds below D at the least and the greatest double in (0, 1) spare
+    // the logarithms: ln(1 / 5e-324) > 744, -ln(1 - nextafter(1, 0)) > 36)
+    *p_lo = target > 0.5 * alpha && kl(alpha, 5e-324) <= target ? 0.0 : lower_root(alpha, beta, target);
+    *p_hi = target > 0.5 * beta && kl(alpha, std::nextafter(1.0, 0.0)) <= target ? 1.0
+                                                                                 : upper_root(alpha, beta, target);
     return PM_OK;
 }
 
