@@ -41,7 +41,8 @@ namespace pm {
 pm_status check_device(const pm_graph *g);
 int sampler_cu_count(int dev);
 pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipStream_t s,
-                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, uint64_t *, hipStream_t));
+                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, uint64_t *, uint64_t *, bool *,
+                                      hipStream_t));
 
 namespace {
 
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_alias(SamplerView g, const Al
         const uint64_t i = base + (uint64_t)lane_id();
         tally_count(cnt, i < k ? alias_sample<CENTERED>(g, T, N, seed, first + i) : kUndecided);
     }
-    tally_flush(cnt, tally, nullptr);
+    tally_flush(cnt, tally, nullptr, 0);
 }
 
 // Draw order for the alias draw: the key is the top bits of the bucket b (the
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_alias_sorted(SamplerView g, c
         const uint64_t j = base + (uint64_t)lane_id();
         tally_count(cnt, j < k ? alias_sample<CENTERED>(g, T, N, seed, first + ids[j]) : kUndecided);
     }
-    tally_flush(cnt, tally, nullptr);
+    tally_flush(cnt, tally, nullptr, 0);
 }
 
 // Buffers of one alias draw-order sort chunk of min(k, kSortedChunk) ids.
@@ -444,7 +445,8 @@ pm_status launch_alias(const pm_graph *g, bool centered, uint64_t seed, uint64_t
     return PM_OK;
 }
 
-pm_status sample_alias_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *, hipStream_t s)
+pm_status sample_alias_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *, uint64_t *, bool *,
+                             hipStream_t s)
 {
     if ((g->R_tau && !g->alias_tau) || (g->R_lam && !g->alias_lam)) {
         set_error("alias draw: the graph has no alias tables (pm_graph_build_alias)");

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_batch(const BatchGraph *__res
             }
         }
         // (the barriers of the next tile's fetch keep its counts apart from these)
-        tally_flush(cnt, tallies + ((uint64_t)T.slot * 2 + T.tag) * PM_NUM_TALLIES, nullptr);
+        tally_flush(cnt, tallies + ((uint64_t)T.slot * 2 + T.tag) * PM_NUM_TALLIES, nullptr, 0);
     }
 }
 

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cstring>
 #include <mutex>
 
 namespace pm {
@@ -42,7 +43,26 @@ __global__ __launch_bounds__(kBlock) void k_sample(SamplerView g, uint64_t seed,
 {
     WaveTally cnt;
     sample_ids<CENTERED, U, SEARCH>(g, seed, first, k, blockIdx.x, gridDim.x, cnt);
-    tally_flush(cnt, tally, parts);
+    tally_flush(cnt, tally, parts, blockIdx.x);
+}
+
+// Both samplers in one launch, the 3-path sampler's `bp` blocks first: at small
+// k the two are bound by the latency of one sample's dependent reads, at
+// larger k the second one's blocks fill the first one's tail.
+template <int U>
+__global__ __launch_bounds__(kBlock) void k_sample_pair(SamplerView vp, SamplerView vc, uint64_t seed,
+                                                        uint64_t first_p, uint64_t kp, uint64_t first_c, uint64_t kc,
+                                                        unsigned bp, unsigned long long *__restrict__ parts_p,
+                                                        unsigned long long *__restrict__ parts_c)
+{
+    WaveTally cnt;
+    if (blockIdx.x < bp) {
+        sample_ids<false, U, PM_SEARCH_HASH>(vp, seed, first_p, kp, blockIdx.x, bp, cnt);
+        tally_flush(cnt, nullptr, parts_p, blockIdx.x);
+    } else {
+        sample_ids<true, U, PM_SEARCH_HASH>(vc, seed, first_c, kc, blockIdx.x - bp, gridDim.x - bp, cnt);
+        tally_flush(cnt, nullptr, parts_c, blockIdx.x - bp);
+    }
 }
 
 // The same samples with the adjacency tests done by the wave together
@@ -64,7 +84,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_wave(SamplerView g, uint64_t 
         const uint32_t cls = sample_class_wave<CENTERED>(g, seed, id, act);
         tally_count(cnt, act ? cls : kUndecided);
     }
-    tally_flush(cnt, tally, parts);
+    tally_flush(cnt, tally, parts, blockIdx.x);
 }
 
 // Sums of the blocks' rows of counts: block 0 the 3-path sampler's, block 1
@@ -216,7 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_sorted(SamplerView g, uint64_
         if (j < k) cls = sample_class<CENTERED, SEARCH>(g, seed, first + ids[j]);
         tally_count(cnt, cls);
     }
-    tally_flush(cnt, tally, parts);
+    tally_flush(cnt, tally, parts, blockIdx.x);
 }
 
 // The ids [first, first + kc) sorted by their draw keys in b's buffers
@@ -465,14 +485,51 @@ static pm_status sample_pair_overlapped(const SampleShape &sh, const pm_graph *g
                         parts[1], s);
 }
 
+// Both samplers in id order as one launch (each of nonzero weight and budget),
+// up to kPairRounds samples per resident lane: pm_count at 1e5 + 1e5 samples
+// took 44 / 60 / 71 / 79 us against 53 / 73 / 85 / 96 with two launches (on
+// 4e4, 2e6, 2e7 and 2.4e8 slots), the same at 4e5 + 4e5, and at 1.6e6 + 1.6e6
+// 616 against 535 us (2e7 slots): the samplers share only part of the graph,
+// and side by side each leaves the other less of the L2.
+constexpr uint64_t kPairRounds = 3;
+
+static pm_status launch_pair(const SampleShape &sh, const pm_graph *g, const pm_params *p, uint64_t *const parts[2],
+                             unsigned rows[2], hipStream_t s)
+{
+    const SamplerView vp = view_of(g, false), vc = view_of(g, true);
+    const uint64_t per = (uint64_t)kBlock * sh.per_lane;
+    rows[0] = (unsigned)std::min<uint64_t>((p->k_path + per - 1) / per, sh.cap);
+    rows[1] = (unsigned)std::min<uint64_t>((p->k_cent + per - 1) / per, sh.cap);
+    unsigned long long *pp = (unsigned long long *)parts[0], *pc = (unsigned long long *)parts[1];
+    const dim3 grid(rows[0] + rows[1]);
+    ProfScope prof("sample_path", s), prof_c("sample_centered", s);  // one launch, timed under both names
+    switch (sh.per_lane) {
+    case 1:
+        hipLaunchKernelGGL(k_sample_pair<1>, grid, dim3(kBlock), 0, s, vp, vc, p->seed, p->first_id_path, p->k_path,
+                           p->first_id_cent, p->k_cent, rows[0], pp, pc);
+        break;
+    case 2:
+        hipLaunchKernelGGL(k_sample_pair<2>, grid, dim3(kBlock), 0, s, vp, vc, p->seed, p->first_id_path, p->k_path,
+                           p->first_id_cent, p->k_cent, rows[0], pp, pc);
+        break;
+    default:
+        hipLaunchKernelGGL(k_sample_pair<4>, grid, dim3(kBlock), 0, s, vp, vc, p->seed, p->first_id_path, p->k_path,
+                           p->first_id_cent, p->k_cent, rows[0], pp, pc);
+        break;
+    }
+    PM_HIP(hipGetLastError());
+    return PM_OK;
+}
+
 // Both samplers' tallies into tallies_dev[2 x PM_NUM_TALLIES].  `scratch`,
 // when given, holds 2 x kMaxTallyParts rows of block counts: where every
 // sampler is one launch of at most so many blocks, the blocks store their
 // counts there and one kernel sums them, so that no launch ends in atomics on
 // one line (a caller without it, whose launches may be captured in a graph,
-// gets one atomic per block and class).
+// gets one atomic per block and class).  The sums go to `pinned` when given
+// (*placed), else to tallies_dev.
 static pm_status sample_into(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *scratch,
-                             hipStream_t s)
+                             uint64_t *pinned, bool *placed, hipStream_t s)
 {
     PM_TRY(check_device(g));
     const SampleShape sh(g);
@@ -485,13 +542,18 @@ static pm_status sample_into(const pm_graph *g, const pm_params *p, uint64_t *ta
     unsigned rows[2] = {0, 0};
     if (pair) {
         PM_TRY(sample_pair_overlapped(sh, g, p, tallies_dev, parts, rows, s));
+    } else if (scratch && sh.mode == PM_SEARCH_HASH && g->R_tau && g->R_lam && p->k_path && p->k_cent &&
+               p->k_path + p->k_cent <= kPairRounds * sh.cap * kBlock) {
+        PM_TRY(launch_pair(sh, g, p, parts, rows, s));
     } else {
         PM_TRY(launch_sampler(sh, g, false, p->seed, p->first_id_path, p->k_path, tallies_dev, s, nullptr, parts[0],
                               &rows[0]));
         PM_TRY(launch_sampler(sh, g, true, p->seed, p->first_id_cent, p->k_cent, tallies_dev + PM_NUM_TALLIES, s,
                               nullptr, parts[1], &rows[1]));
     }
-    return scratch ? sum_tallies(parts[0], rows[0], parts[1], rows[1], tallies_dev, s) : PM_OK;
+    if (!scratch) return PM_OK;
+    *placed = pinned != nullptr;
+    return sum_tallies(parts[0], rows[0], parts[1], rows[1], pinned ? pinned : tallies_dev, s);
 }
 
 pm_status sample_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, hipStream_t s)
@@ -500,7 +562,8 @@ pm_status sample_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_
         set_error("null argument");
         return PM_EINVAL;
     }
-    return sample_into(g, p, tallies_dev, nullptr, s);
+    bool placed = false;
+    return sample_into(g, p, tallies_dev, nullptr, nullptr, &placed, s);
 }
 
 __global__ void k_philox(const uint32_t *in, uint32_t *out, int64_t count)
@@ -632,11 +695,47 @@ pm_status check_device(const pm_graph *g)
     return PM_OK;
 }
 
-// Run both samplers of one graph through `run` (which fills 2 x PM_NUM_TALLIES
-// device tallies, with 2 x kMaxTallyParts rows of scratch), read the tallies
-// back and finalize.
+// Pinned host memory for the tallies of kHostSlots calls at a time, one block
+// for the life of the process (portable: every device writes it).  A call
+// that finds no free slot, or no pinned memory, takes device memory and copies.
+struct HostTallies {
+    static constexpr int kSlots = 32;
+    std::mutex mu;
+    bool tried = false;
+    uint64_t *base = nullptr;
+    uint32_t used = 0;  // one bit per slot
+
+    uint64_t *take()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (!tried) {
+            tried = true;
+            void *q = nullptr;
+            if (hipHostMalloc(&q, sizeof(uint64_t) * 2 * PM_NUM_TALLIES * kSlots, hipHostMallocPortable) == hipSuccess)
+                base = (uint64_t *)q;
+            else
+                (void)hipGetLastError();
+        }
+        if (!base || used == 0xFFFFFFFFu) return nullptr;
+        const int i = __builtin_ctz(~used);
+        used |= 1u << i;
+        return base + (size_t)i * 2 * PM_NUM_TALLIES;
+    }
+    void give(uint64_t *p)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        used &= ~(1u << (int)((p - base) / (2 * PM_NUM_TALLIES)));
+    }
+};
+static HostTallies g_host_tallies;
+
+// Run both samplers of one graph through `run`, which fills 2 x PM_NUM_TALLIES
+// device tallies, with 2 x kMaxTallyParts rows of scratch -- or, when its last
+// step is one kernel's plain stores, `pinned` (if not null) instead, setting
+// *placed -- and finalize.
 pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipStream_t s,
-                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, uint64_t *, hipStream_t))
+                     pm_status (*run)(const pm_graph *, const pm_params *, uint64_t *, uint64_t *, uint64_t *, bool *,
+                                      hipStream_t))
 {
     if (!g || !p || !out) {
         set_error("null argument");
@@ -651,19 +750,27 @@ pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipS
         return PM_EINVAL;
     }
     PM_TRY(check_device(g));
-    uint64_t *t = nullptr;
-    PM_TRY(dev_alloc((void **)&t, 2 * (kMaxTallyParts + 1) * PM_NUM_TALLIES * sizeof(uint64_t), s));
-    uint64_t host[2 * PM_NUM_TALLIES];
-    pm_status st = run(g, p, t, t + 2 * PM_NUM_TALLIES, s);
+    uint64_t *t = nullptr, host[2 * PM_NUM_TALLIES], *pinned = g_host_tallies.take();
+    pm_status st = dev_alloc((void **)&t, 2 * (kMaxTallyParts + 1) * PM_NUM_TALLIES * sizeof(uint64_t), s);
     if (st == PM_OK) {
-        hipError_t e = hipMemcpyAsync(host, t, sizeof(host), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) {
+        bool placed = false;
+        st = run(g, p, t, t + 2 * PM_NUM_TALLIES, pinned, &placed, s);
+        hipError_t e = hipSuccess;
+        if (st == PM_OK && !placed)
+            e = hipMemcpyAsync(pinned ? pinned : host, t, sizeof(host), hipMemcpyDeviceToHost, s);
+        // also after a failure: a slot is given back only when nothing writes it
+        const hipError_t w = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = w;
+        if (st == PM_OK && e != hipSuccess) {
             set_error(std::string("pm_count: ") + hipGetErrorString(e));
             st = PM_EDEVICE;
         }
+        dev_free(t, s);
     }
-    dev_free(t, s);
+    if (pinned) {
+        std::memcpy(host, pinned, sizeof(host));
+        g_host_tallies.give(pinned);
+    }
     if (st != PM_OK) return st;
     return finalize(host, host + PM_NUM_TALLIES, g->R_tau / 2, g->R_lam / 2, g->N1, p->k_path, p->k_cent, p->delta,
                     out);

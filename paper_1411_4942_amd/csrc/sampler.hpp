@@ -247,15 +247,16 @@ __device__ __forceinline__ void tally_count(WaveTally &t, uint32_t cls)
     for (int c = 0; c < PM_NUM_TALLIES; ++c) t.c[c] += (uint32_t)__popcll(__ballot(cls == (uint32_t)c));
 }
 
-// The block's counts: with `parts`, stored as the block's row of it
-// (parts[blockIdx.x * PM_NUM_TALLIES + c], summed by k_tally_sum); without,
+// The block's counts: with `parts`, stored as row `row` of it
+// (parts[row * PM_NUM_TALLIES + c], summed by k_tally_sum); without,
 // added to `tally`, one atomic per class.  Every thread of the block calls it.
 // Adding every wave's counts straight to `tally` bounded the launches: atomics
 // on one line take 5.9 ns each, and the 1564 waves x 6 classes of 1e5 3-path
 // samples 55 us.  With rows and their sum, pm_count went from 135 to 71 us at
 // 1e5 + 1e5 samples (Erdos-Renyi, 4e4 slots), 946 to 668 us at 2e6 + 2e6
 // (Chung-Lu, 2e7 slots) and 2858 to 2599 us at 1e7 + 1e7 (R-MAT scale 22).
-__device__ __forceinline__ void tally_flush(const WaveTally &t, unsigned long long *tally, unsigned long long *parts)
+__device__ __forceinline__ void tally_flush(const WaveTally &t, unsigned long long *tally, unsigned long long *parts,
+                                            unsigned row)
 {
     __shared__ unsigned long long s_tally[kBlock / kWave][PM_NUM_TALLIES];
     if (lane_id() == 0) {
@@ -268,7 +269,7 @@ __device__ __forceinline__ void tally_flush(const WaveTally &t, unsigned long lo
 #pragma unroll
         for (int w = 0; w < kBlock / kWave; ++w) v += s_tally[w][threadIdx.x];
         if (parts)
-            parts[(uint64_t)blockIdx.x * PM_NUM_TALLIES + threadIdx.x] = v;
+            parts[(uint64_t)row * PM_NUM_TALLIES + threadIdx.x] = v;
         else if (v)
             atomicAdd(&tally[threadIdx.x], v);
     }
