@@ -188,19 +188,9 @@ pm_status pm_count_motifs(const pm_csr_view *csr, uint64_t k, uint64_t seed, pm_
         p.seed = seed;
         p.delta = 0.01;
         st = pm::count_on_graph(g, &p, out, nullptr);
-        // samplers may still read the graph on a caller's stream
-        // (pm_sample_async): wait for the whole device before freeing
-        hipError_t e = hipDeviceSynchronize();
-        if (e != hipSuccess) {
-            pm::set_error(std::string("pm_graph_destroy: ") + hipGetErrorString(e));
-            return PM_EDEVICE;
-        }
+        // nothing else has the graph, and the count has waited for the samplers:
+        // the memory goes back to the library's cache behind the null stream
         pm::graph_free(g, nullptr);
-        e = hipStreamSynchronize(nullptr);
-        if (st == PM_OK && e != hipSuccess) {
-            pm::set_error(std::string("pm_count_motifs: ") + hipGetErrorString(e));
-            return PM_EDEVICE;
-        }
         return st;
     })
 }

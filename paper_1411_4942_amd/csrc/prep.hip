@@ -31,12 +31,27 @@ enum : uint32_t {
     ERR_GUIDE = 128u,  // guide write out of range: only from inconsistent weights
 };
 
+// Row size classes: class c holds the rows with bound[c] < degree <=
+// bound[c + 1] (the last one without an upper bound).
+constexpr int kRowClasses = 10;
+__host__ __device__ constexpr uint32_t row_bound(int c)
+{
+    constexpr uint32_t b[kRowClasses] = {0u, 16u, 64u, 128u, 256u, 1024u, 4096u, 8192u, 16384u, 32768u};
+    return b[c];
+}
+
+// rows and slots of one class, on a line of their own (one pair of atomics
+// per block of k_degrees)
+struct alignas(128) ClassLine {
+    unsigned long long rows, slots;
+};
+
 struct PrepStats {
     uint32_t err;
     uint32_t dmax;
-    uint64_t isolated;
     uint64_t n1_lo;
     uint64_t n1_hi;
+    int64_t first, slots;  // off[0] and off[n] of the input
     uint32_t nlong_tau;
     uint32_t nlong_lam;
     U64x2 totals;        // (2W, 2 Lambda) as summed by the weights scan
@@ -44,7 +59,9 @@ struct PrepStats {
     uint32_t shift_lam;
     uint64_t nb_tau;     // guide buckets of each sampler
     uint64_t nb_lam;
+    ClassLine cls[kRowClasses + 1];  // isolated vertices, then the classes
 };
+static_assert(sizeof(PrepStats) <= HostSlot::kBytes && sizeof(PrepStats) % 4 == 0, "read back through one slot");
 
 // Guide shape: the smallest bucket width 2^shift with at most `target`
 // buckets over [0, R) (target >= 2, so shift <= 63).  Same on host and device.
@@ -64,36 +81,98 @@ __host__ __device__ inline uint64_t guide_target(int64_t slots)
 // kernels
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kBlock) void k_degrees(const int64_t *__restrict__ off, int64_t n, int64_t slots,
+// What the degrees alone determine, in one pass: the degree array and its
+// largest, N_1 = sum_v C(d_v, 3) in 128 bits, and the rows and slots of every
+// size class (rows ascend by degree, so these place the classes).  One block's
+// sums go out with one atomic each; offsets outside [0, off[n]] or decreasing
+// set ERR_OFFSETS (their degrees count as 0).
+__global__ __launch_bounds__(kBlock) void k_degrees(const int64_t *__restrict__ off, int64_t n,
                                                     uint32_t *__restrict__ deg, PrepStats *st)
 {
-    uint32_t err = 0, dmax = 0;
+    __shared__ unsigned long long s_rows[kRowClasses + 1], s_slots[kRowClasses + 1];
+    __shared__ uint32_t s_max, s_err;
+    __shared__ uint64_t s_lo[kBlock / kWave], s_hi[kBlock / kWave];
+    if (threadIdx.x <= kRowClasses) s_rows[threadIdx.x] = s_slots[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_max = s_err = 0;
+    __syncthreads();
+    const int64_t slots = off[n];
+    uint32_t err = 0, dmax = 0, rows[kRowClasses + 1] = {0};
+    uint64_t sl[kRowClasses + 1] = {0};
+    unsigned __int128 acc = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        int64_t a = off[v], b = off[v + 1];
-        if (a < 0 || b < a || b > slots) {
+        const int64_t a = off[v], b = off[v + 1];
+        uint32_t d = 0;
+        if (a < 0 || b < a || b > slots)
             err |= ERR_OFFSETS;
-            deg[v] = 0;
-            continue;
-        }
-        uint32_t d = (uint32_t)(b - a);
+        else
+            d = (uint32_t)(b - a);
         deg[v] = d;
         dmax = d > dmax ? d : dmax;
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < kRowClasses; ++q) c += d > row_bound(q);
+#pragma unroll
+        for (int q = 0; q <= kRowClasses; ++q) {
+            rows[q] += c == q;
+            sl[q] += c == q ? d : 0u;
+        }
+        if (d >= 3) {
+            // C(d,3) = d (d-1) (d-2) / 6: divide the factors first, exactly
+            uint64_t x = d, y = d - 1, z = d - 2;
+            if (x % 3 == 0) x /= 3; else if (y % 3 == 0) y /= 3; else z /= 3;
+            if ((x & 1) == 0) x >>= 1; else if ((y & 1) == 0) y >>= 1; else z >>= 1;
+            acc += (unsigned __int128)(x * y) * z;
+        }
     }
-    if (err) atomicOr(&st->err, err);
+    uint64_t lo = (uint64_t)acc, hi = (uint64_t)(acc >> 64);
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
-        uint32_t x = __shfl_xor(dmax, o, kWave);
-        dmax = x > dmax ? x : dmax;
+        const uint64_t olo = __shfl_xor(lo, o, kWave), ohi = __shfl_xor(hi, o, kWave);
+        const uint64_t nlo = lo + olo;
+        hi = hi + ohi + (nlo < lo ? 1u : 0u);
+        lo = nlo;
     }
-    // one atomic per block: contention on st->dmax, not bandwidth, bounds this kernel
-    __shared__ uint32_t s_max[kBlock / kWave];
-    if (lane_id() == 0) s_max[threadIdx.x / kWave] = dmax;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t m = 0;
 #pragma unroll
-        for (int i = 0; i < kBlock / kWave; ++i) m = s_max[i] > m ? s_max[i] : m;
-        if (m) atomicMax(&st->dmax, m);
+    for (int q = 0; q <= kRowClasses; ++q) {
+        const uint32_t r = wave_sum_u32(rows[q]);
+        uint64_t x = sl[q];
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
+        if (lane_id() == 0 && r) {
+            atomicAdd(&s_rows[q], (unsigned long long)r);
+            atomicAdd(&s_slots[q], (unsigned long long)x);
+        }
+    }
+    if (lane_id() == 0) {
+        s_lo[threadIdx.x / kWave] = lo;
+        s_hi[threadIdx.x / kWave] = hi;
+    }
+    atomicMax(&s_max, dmax);
+    if (err) atomicOr(&s_err, err);
+    __syncthreads();
+    if (threadIdx.x <= kRowClasses && s_rows[threadIdx.x]) {
+        atomicAdd(&st->cls[threadIdx.x].rows, s_rows[threadIdx.x]);
+        atomicAdd(&st->cls[threadIdx.x].slots, s_slots[threadIdx.x]);
+    }
+    if (threadIdx.x == kWave) {
+        if (s_max) atomicMax(&st->dmax, s_max);
+        if (s_err) atomicOr(&st->err, s_err);
+        if (blockIdx.x == 0) {
+            st->first = off[0];
+            st->slots = slots;
+        }
+        lo = s_lo[0];
+        hi = s_hi[0];
+        for (int i = 1; i < kBlock / kWave; ++i) {
+            const uint64_t nlo = lo + s_lo[i];
+            hi += s_hi[i] + (nlo < lo ? 1u : 0u);
+            lo = nlo;
+        }
+        if (lo | hi) {
+            const unsigned long long old = atomicAdd((unsigned long long *)&st->n1_lo, (unsigned long long)lo);
+            const uint64_t carry = (old + lo < old) ? 1u : 0u;
+            if (hi + carry) atomicAdd((unsigned long long *)&st->n1_hi, (unsigned long long)(hi + carry));
+        }
     }
 }
 
@@ -108,8 +187,12 @@ struct DegIn {
     __device__ __forceinline__ uint64_t operator()(int64_t i) const { return d[i]; }
 };
 struct OffOut {
-    uint32_t *off;  // writes off[i+1] (below 2^32: the slot count is)
-    __device__ __forceinline__ void operator()(int64_t i, uint64_t incl, uint64_t) const { off[i + 1] = (uint32_t)incl; }
+    uint32_t *off;  // writes off[i+1] (below 2^32: the slot count is), and off[0]
+    __device__ __forceinline__ void operator()(int64_t i, uint64_t incl, uint64_t) const
+    {
+        if (i == 0) off[0] = 0u;
+        off[i + 1] = (uint32_t)incl;
+    }
 };
 
 // ---------------------------------------------------------------------------
@@ -723,40 +806,18 @@ __global__ __launch_bounds__(kBlock) void k_hub_merge(const uint32_t *__restrict
     }
 }
 
-// first row of each size class (degrees ascend along the new order): cls[c]
-// = first row with degree > {0, 16, 64, 128, 256, 1024, 4096, 8192, 16384,
-// 32768}[c]; cls[10] = the first slot of row cls[9]
-constexpr int kRowClasses = 10;
-__global__ void k_row_classes(const uint32_t *__restrict__ deg, const uint32_t *__restrict__ off, int64_t n,
-                              int64_t *cls)
+// ladder levels 2 .. top (level 1 comes with the rows): level l holds
+// col[i 32^l]
+struct LadderLevels {
+    uint32_t *base;
+    uint64_t at[8], count[8];  // start and entries of each level
+    int top;
+};
+__global__ __launch_bounds__(kBlock) void k_ladder_levels(const uint32_t *__restrict__ col, LadderLevels L)
 {
-    const uint32_t bound[kRowClasses] = {0u, 16u, 64u, 128u, 256u, 1024u, 4096u, 8192u, 16384u, 32768u};
-    const int c = threadIdx.x;
-    if (c >= kRowClasses) return;
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {  // first row with deg > bound[c]
-        const int64_t mid = (lo + hi) >> 1;
-        if (deg[mid] > bound[c])
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    cls[c] = lo;
-    cls[kRowClasses + 1 + c] = off[lo];  // first slot of the class's rows
-    if (c == kRowClasses - 1) cls[kRowClasses] = off[lo];
-}
-
-// ladder level l from level l-1: next[i] = prev[32 i]
-__global__ void k_ladder_level(const uint32_t *__restrict__ prev, int64_t count, uint32_t *__restrict__ next)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-        next[i] = prev[i * 32];
-}
-
-__global__ void k_copy_u32(const uint32_t *__restrict__ a, uint32_t *__restrict__ b, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        b[i] = a[i];
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    for (int l = 2; l <= L.top; ++l)
+        for (uint64_t i = t; i < L.count[l]; i += step) L.base[L.at[l] + i] = col[i << (5 * l)];
 }
 
 // Weights of a slot s = (u, v) with reverse slot r (Sections 3 and 4):
@@ -904,10 +965,11 @@ __device__ __forceinline__ void guide_fill(uint64_t prev, uint64_t cur, uint32_t
 
 
 // guide shape from the totals, and the sentinel guide[nb] = last slot
-__global__ void k_guide_setup(PrepStats *st, int64_t slots, uint32_t *guide_tau, uint32_t *guide_lam)
+__device__ __forceinline__ void guide_setup(PrepStats *st, U64x2 totals, int64_t slots, uint32_t *guide_tau,
+                                            uint32_t *guide_lam)
 {
     const uint64_t target = guide_target(slots);
-    const uint64_t Rt = st->totals.a, Rl = st->totals.b;
+    const uint64_t Rt = totals.a, Rl = totals.b;
     const uint32_t sht = Rt ? guide_shift(Rt, target) : 0u, shl = Rl ? guide_shift(Rl, target) : 0u;
     const uint64_t nbt = Rt ? ((Rt - 1) >> sht) + 1 : 0, nbl = Rl ? ((Rl - 1) >> shl) + 1 : 0;
     st->shift_tau = sht;
@@ -916,6 +978,27 @@ __global__ void k_guide_setup(PrepStats *st, int64_t slots, uint32_t *guide_tau,
     st->nb_lam = nbl;
     if (Rt) guide_tau[nbt] = (uint32_t)(slots - 1);
     if (Rl) guide_lam[nbl] = (uint32_t)(slots - 1);
+}
+
+__global__ void k_guide_setup(PrepStats *st, int64_t slots, uint32_t *guide_tau, uint32_t *guide_lam)
+{
+    guide_setup(st, st->totals, slots, guide_tau, guide_lam);
+}
+
+// Launch 2 for few segments, one block: the segment scan and the guide shape
+// (instead of three scan launches and k_guide_setup).
+constexpr int64_t kOneBlockScan = 32768;
+
+__global__ __launch_bounds__(1024) void k_seg_scan(SegIn in, SegOut out, int64_t nseg, PrepStats *st, int64_t slots,
+                                                   uint32_t *guide_tau, uint32_t *guide_lam)
+{
+    const U64x2 total = scan_one_block(in, out, nseg, PairSumOp(), U64x2{0, 0});
+    if (threadIdx.x == 0) guide_setup(st, total, slots, guide_tau, guide_lam);
+}
+
+__global__ __launch_bounds__(1024) void k_off_scan(DegIn in, OffOut out, int64_t n)
+{
+    (void)scan_one_block(in, out, n, SumOp<uint64_t>(), (uint64_t)0);
 }
 
 // Launch 3 of the weights scan: the guide entries from the global prefixes
@@ -944,10 +1027,10 @@ __global__ __launch_bounds__(kBlock) void k_guide_fill(const uint64_t *__restric
                                                        uint32_t *__restrict__ long_lam, uint32_t long_cap,
                                                        PrepStats *st)
 {
-    // an asymmetric input (found by the weights kernel) leaves the weights
-    // inconsistent, so their bucket ranges could overlap without bound; the
-    // build fails anyway, so the guide is not filled
-    if (st->err & ERR_ASYM) return;
+    // an input that failed a check (of the rows, or the weights kernel's for
+    // symmetry) leaves the weights inconsistent, so their bucket ranges could
+    // overlap without bound; the build fails anyway, so the guide is not filled
+    if (st->err) return;
     const int w = threadIdx.x / kWave;
     const int lane = lane_id();
     const int64_t wave_base = (int64_t)blockIdx.x * (kBlock * kWItems) + (int64_t)w * (kWave * kWItems);
@@ -1010,73 +1093,27 @@ __global__ __launch_bounds__(kBlock) void k_guide_fill(const uint64_t *__restric
     if (err) atomicOr(&st->err, err);
 }
 
-// N_1 = sum_v C(d_v, 3) in 128 bits; isolated vertices.  One pair of
-// atomics per block.
-__global__ __launch_bounds__(kBlock) void k_n1(const uint32_t *__restrict__ deg, int64_t n, PrepStats *st)
+// The long runs of both guides (grid row 0 the 3-path sampler's, 1 the
+// centered one's).
+struct GuideLong {
+    const uint64_t *P, *seg;
+    uint32_t *guide;
+    const uint32_t *list;
+};
+__global__ __launch_bounds__(kBlock) void k_guide_long(GuideLong gt, GuideLong gl, uint32_t cap, const PrepStats *st)
 {
-    __shared__ uint64_t s_lo[kBlock / kWave], s_hi[kBlock / kWave], s_iso[kBlock / kWave];
-    unsigned __int128 acc = 0;
-    uint64_t iso = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        uint64_t d = deg[v];
-        iso += d == 0;
-        if (d >= 3) {
-            // C(d,3) = d (d-1) (d-2) / 6: divide the factors first, exactly
-            uint64_t a = d, b = d - 1, c = d - 2;
-            if (a % 3 == 0) a /= 3; else if (b % 3 == 0) b /= 3; else c /= 3;
-            if ((a & 1) == 0) a >>= 1; else if ((b & 1) == 0) b >>= 1; else c >>= 1;
-            acc += (unsigned __int128)(a * b) * c;
-        }
-    }
-    uint64_t lo = (uint64_t)acc, hi = (uint64_t)(acc >> 64);
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        uint64_t olo = __shfl_xor(lo, o, kWave), ohi = __shfl_xor(hi, o, kWave);
-        uint64_t nlo = lo + olo;
-        hi = hi + ohi + (nlo < lo ? 1u : 0u);
-        lo = nlo;
-        iso += __shfl_xor(iso, o, kWave);
-    }
-    const int w = threadIdx.x / kWave;
-    if (lane_id() == 0) {
-        s_lo[w] = lo;
-        s_hi[w] = hi;
-        s_iso[w] = iso;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        lo = s_lo[0];
-        hi = s_hi[0];
-        iso = s_iso[0];
-        for (int i = 1; i < kBlock / kWave; ++i) {
-            uint64_t nlo = lo + s_lo[i];
-            hi += s_hi[i] + (nlo < lo ? 1u : 0u);
-            lo = nlo;
-            iso += s_iso[i];
-        }
-        unsigned long long old = atomicAdd((unsigned long long *)&st->n1_lo, (unsigned long long)lo);
-        uint64_t carry = (old + lo < old) ? 1u : 0u;
-        atomicAdd((unsigned long long *)&st->n1_hi, (unsigned long long)(hi + carry));
-        atomicAdd((unsigned long long *)&st->isolated, (unsigned long long)iso);
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_guide_long(const uint64_t *__restrict__ P,
-                                                       const uint64_t *__restrict__ seg, const uint32_t *shift_p,
-                                                       uint32_t *__restrict__ guide,
-                                                       const uint32_t *__restrict__ long_list,
-                                                       const uint32_t *nlong, uint32_t cap, const uint32_t *err)
-{
-    if (*err & (ERR_ASYM | ERR_GUIDE)) return;  // inconsistent weights: the build fails
-    const uint32_t shift = *shift_p;
+    if (st->err) return;  // inconsistent weights: the build fails
+    const GuideLong &g = blockIdx.y ? gl : gt;
+    const uint32_t shift = blockIdx.y ? st->shift_lam : st->shift_tau;
+    const uint32_t nlong = blockIdx.y ? st->nlong_lam : st->nlong_tau;
     const uint64_t mask = (shift == 0) ? 0ull : ((1ull << shift) - 1ull);
-    const uint32_t cnt = *nlong < cap ? *nlong : cap;  // listed runs were checked against nb
+    const uint32_t cnt = nlong < cap ? nlong : cap;  // listed runs were checked against nb
     for (uint32_t e = blockIdx.x; e < cnt; e += gridDim.x) {
-        uint32_t s = long_list[e];
-        uint64_t prev = s > 0 ? global_prefix(P, seg, s - 1) : 0ull, cur = global_prefix(P, seg, s);
-        uint64_t j0 = (prev >> shift) + ((prev & mask) != 0 ? 1u : 0u);
-        uint64_t j1 = (cur - 1) >> shift;
-        for (uint64_t j = j0 + threadIdx.x; j <= j1; j += blockDim.x) guide[j] = s;
+        const uint32_t s = g.list[e];
+        const uint64_t prev = s > 0 ? global_prefix(g.P, g.seg, s - 1) : 0ull, cur = global_prefix(g.P, g.seg, s);
+        const uint64_t j0 = (prev >> shift) + ((prev & mask) != 0 ? 1u : 0u);
+        const uint64_t j1 = (cur - 1) >> shift;
+        for (uint64_t j = j0 + threadIdx.x; j <= j1; j += blockDim.x) g.guide[j] = s;
     }
 }
 
@@ -1110,6 +1147,10 @@ void graph_free(pm_graph *g, hipStream_t s)
     dev_free_batch(arrays, sizeof(arrays) / sizeof(arrays[0]), s);
     delete g;
 }
+
+// The row hash is built beside the reverse sort and the weights pass from this
+// many slots on.
+constexpr int64_t kBesideSlots = 1ll << 22;
 
 // The row hash (rowhash.hip): `parts` is kRowHashSmall, kRowHashWide or both.
 pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t slot_at[5], uint32_t *H,
@@ -1148,17 +1189,30 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     ProfScope prof_total("prep_total", s);
     Temps tmp(s);
 
-    // offsets bounds from the host side
-    int64_t first = 0, slots = 0;
-    if (csr->on_device) {
-        PM_HIP(hipMemcpyAsync(&first, csr->row_offsets, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        PM_HIP(hipMemcpyAsync(&slots, csr->row_offsets + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        PM_HIP(hipStreamSynchronize(s));
-    } else {
-        first = csr->row_offsets[0];
-        slots = csr->row_offsets[n];
+    HostSlot slot;
+    const int64_t nn = std::max<int64_t>(n, 1);
+    const int64_t *off_in = csr->row_offsets;
+    if (!csr->on_device) {
+        int64_t *o = nullptr;
+        PM_TRY(tmp.get(&o, (size_t)n + 1));
+        PM_HIP(hipMemcpyAsync(o, csr->row_offsets, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s));
+        off_in = o;
     }
-    if (first != 0 || slots < 0) {
+    PrepStats *st = nullptr, hst;
+    uint32_t *deg_in = nullptr;
+    PM_TRY(tmp.get(&st, 1));
+    PM_TRY(tmp.get(&deg_in, nn));
+    PM_TRY(fill_async<uint32_t>((uint32_t *)st, 0u, sizeof(PrepStats) / 4, s));
+    {
+        ProfScope prof("degrees", s);
+        hipLaunchKernelGGL(k_degrees, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, off_in, n, deg_in, st);
+        PM_HIP(hipGetLastError());
+    }
+    // the row walk below trusts the offsets: read the verdict first, and with
+    // it the sizes of everything that follows
+    PM_HIP(slot.read_back(&hst, st, sizeof(hst), s));
+    const int64_t slots = hst.slots;
+    if (hst.first != 0 || slots < 0) {
         set_error(err_text(ERR_OFFSETS));
         return PM_EGRAPH;
     }
@@ -1170,18 +1224,28 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         set_error("null cols");
         return PM_EINVAL;
     }
-
-    const int64_t *off_in = csr->row_offsets;
+    if (hst.err) {
+        set_error(err_text(hst.err));
+        return PM_EGRAPH;
+    }
+    const int64_t ss = std::max<int64_t>(slots, 1);
     const int32_t *col_in = csr->cols;
     if (!csr->on_device) {
-        int64_t *o = nullptr;
         int32_t *c = nullptr;
-        PM_TRY(tmp.get(&o, (size_t)n + 1));
-        PM_TRY(tmp.get(&c, (size_t)std::max<int64_t>(slots, 1)));
-        PM_HIP(hipMemcpyAsync(o, csr->row_offsets, sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, s));
+        PM_TRY(tmp.get(&c, (size_t)ss));
         if (slots > 0) PM_HIP(hipMemcpyAsync(c, csr->cols, sizeof(int32_t) * slots, hipMemcpyHostToDevice, s));
-        off_in = o;
         col_in = c;
+    }
+    // first row of each size class (the rows above its bound), then the first
+    // slots of the hub rows' and of every class's rows
+    int64_t cls[2 * kRowClasses + 1];
+    {
+        int64_t rows = 0, sl = 0;
+        for (int c = 0; c < kRowClasses; ++c) {
+            cls[c] = rows += (int64_t)hst.cls[c].rows;
+            cls[kRowClasses + 1 + c] = sl += (int64_t)hst.cls[c].slots;
+        }
+        cls[kRowClasses] = sl;
     }
 
     pm_graph *g = new (std::nothrow) pm_graph();
@@ -1198,51 +1262,38 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     g->n = n;
     g->slots = slots;
 
-    PrepStats *st = nullptr;
-    PM_TRY(tmp.get(&st, 1));
-    PM_TRY(fill_async<uint32_t>((uint32_t *)st, 0u, sizeof(PrepStats) / 4, s));
-    PrepStats hst;
-
-    const int64_t nn = std::max<int64_t>(n, 1), ss = std::max<int64_t>(slots, 1);
-    uint32_t *deg_in = nullptr;
-    PM_TRY(tmp.get(&deg_in, nn));
-    if (n > 0) {
-        ProfScope prof("degrees", s);
-        hipLaunchKernelGGL(k_degrees, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, off_in, n, slots, deg_in, st);
-        PM_HIP(hipGetLastError());
-    }
-    // the row walk below trusts the offsets: read the verdict first
-    PM_HIP(hipMemcpyAsync(&hst, st, sizeof(hst), hipMemcpyDeviceToHost, s));
-    PM_HIP(hipStreamSynchronize(s));
-    if (hst.err) {
-        set_error(err_text(hst.err));
-        return PM_EGRAPH;
-    }
     g->dmax = hst.dmax;
 
-    // vertex order: stable sort of ids by degree
+    // vertex order: stable sort of ids by degree (the sorted degrees end in
+    // g->deg)
     char *rscr = nullptr;
     PM_TRY(tmp.get(&rscr, radix_scratch_bytes(std::max<int64_t>(slots, n))));
-    uint32_t *vk0, *vv0, *vk1, *vv1;
-    PM_TRY(tmp.get(&vk0, nn));
-    PM_TRY(tmp.get(&vv0, nn));
-    PM_TRY(tmp.get(&vk1, nn));
-    PM_TRY(tmp.get(&vv1, nn));
-    uint32_t *sorted_deg, *order;
-    PM_TRY(radix_sort("vertex_sort", RadixKeys{deg_in}, vk0, vv0, vk1, vv1, n, bits_for((uint64_t)g->dmax), rscr, s,
-                      &sorted_deg, &order));
-
+    uint32_t *vk = nullptr, *vv0, *vv1 = nullptr;
     PM_TRY(dev_alloc((void **)&g->rank, sizeof(int32_t) * nn, s));
     PM_TRY(dev_alloc((void **)&g->deg, sizeof(uint32_t) * nn, s));
     PM_TRY(dev_alloc((void **)&g->off, sizeof(uint32_t) * (n + 1), s));
     g->bytes += sizeof(int32_t) * nn + sizeof(uint32_t) * nn + sizeof(uint32_t) * (n + 1);
+    const int dbits = bits_for((uint64_t)g->dmax);
+    const int dpasses = RadixDigits(dbits).passes;
+    PM_TRY(tmp.get(&vv0, nn));
+    if (dpasses > 1) {
+        PM_TRY(tmp.get(&vk, nn));
+        PM_TRY(tmp.get(&vv1, nn));
+    }
+    uint32_t *const k_odd = dpasses & 1 ? g->deg : vk, *const k_even = dpasses & 1 ? vk : g->deg;
+    uint32_t *sorted_deg, *order;
+    PM_TRY(radix_sort("vertex_sort", RadixKeys{deg_in}, k_odd, vv0, k_even, vv1, n, dbits, rscr, s, &sorted_deg,
+                      &order));
     if (n > 0) {
         hipLaunchKernelGGL(k_rank_from_order, dim3(grid_stream(n)), dim3(kBlock), 0, s, order, g->rank, n);
-        hipLaunchKernelGGL(k_copy_u32, dim3(grid_stream(n)), dim3(kBlock), 0, s, sorted_deg, g->deg, n);
         PM_HIP(hipGetLastError());
     }
-    PM_TRY(fill_async<uint32_t>(g->off, 0u, 1, s));
-    {
+    if (n == 0) {
+        PM_TRY(fill_async<uint32_t>(g->off, 0u, 1, s));
+    } else if (n <= kOneBlockScan) {
+        hipLaunchKernelGGL(k_off_scan, dim3(1), dim3(1024), 0, s, DegIn{g->deg}, OffOut{g->off}, n);
+        PM_HIP(hipGetLastError());
+    } else {
         char *scr = nullptr;
         PM_TRY(tmp.get(&scr, ScanScratch<uint64_t>::bytes_for(n, 16)));
         PM_TRY((scan_launch<uint64_t, 16>(DegIn{g->deg}, OffOut{g->off}, n, SumOp<uint64_t>(), 0ull, scr, s)));
@@ -1277,14 +1328,7 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     uint32_t *ladder1 = g->ladder_top > 0 ? g->ladder + g->ladder_off[1] : nullptr;
 
     // the rows, sorted where they are built (by size class)
-    int64_t cls[2 * kRowClasses + 1] = {0};  // first row of each class, then the hub rows' and classes' first slots
     if (slots > 0) {
-        int64_t *cls_d = nullptr;
-        PM_TRY(tmp.get(&cls_d, 2 * kRowClasses + 1));
-        hipLaunchKernelGGL(k_row_classes, dim3(1), dim3(kWave), 0, s, g->deg, g->off, n, cls_d);
-        PM_HIP(hipGetLastError());
-        PM_HIP(hipMemcpyAsync(cls, cls_d, sizeof(cls), hipMemcpyDeviceToHost, s));
-        PM_HIP(hipStreamSynchronize(s));
         ProfScope prof("build_rows", s);
         // the rows above 8192 (one block of 1024 per row or chunk, whose few
         // large blocks leave CUs idle at the ends of their launches) run on two
@@ -1302,7 +1346,7 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         }
         hipStream_t side[2];
         PM_HIP(side_streams(side));
-        Fork fork(s, side, 2);
+        Fork fork(s, side, n > cls[7] ? 2 : 0);  // (no such rows: nothing to join)
         PM_HIP(fork.status);
         if (cls[8] > cls[7]) {
             ProfScope pc("build_rows.b16384", side[1]);
@@ -1376,21 +1420,19 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         PM_HIP(fork.join());  // before anything can return: the temporaries are released on s
         PM_HIP(launched);
     }
-    tmp.release(vk0);
-    tmp.release(vv0);
-    tmp.release(vk1);
-    tmp.release(vv1);
-    // the reverse sort and the weights trust the columns: read the slot checks
-    PM_HIP(hipMemcpyAsync(&hst, st, sizeof(hst), hipMemcpyDeviceToHost, s));
-    PM_HIP(hipStreamSynchronize(s));
-    if (hst.err) {
-        set_error(err_text(hst.err));
-        return PM_EGRAPH;
-    }
-    for (int l = 2; l <= g->ladder_top; ++l) {
-        const int64_t cnt = (int64_t)ladder_count(slots, l);
-        hipLaunchKernelGGL(k_ladder_level, dim3(grid_for(cnt, kBlock, 1024)), dim3(kBlock), 0, s,
-                           g->ladder + g->ladder_off[l - 1], cnt, g->ladder + g->ladder_off[l]);
+    // (the row checks are read back with the others at the end: the columns are
+    // vertex ids whatever the input held, the sort and the weights' reads stay
+    // in range with any of them, and the guide is not filled after an error)
+    if (g->ladder_top > 1) {
+        LadderLevels L{};
+        L.base = g->ladder;
+        L.top = g->ladder_top;
+        for (int l = 2; l <= L.top; ++l) {
+            L.at[l] = g->ladder_off[l];
+            L.count[l] = ladder_count(slots, l);
+        }
+        hipLaunchKernelGGL(k_ladder_levels, dim3(grid_for((int64_t)L.count[2], kBlock, 1024)), dim3(kBlock), 0, s,
+                           g->col, L);
         PM_HIP(hipGetLastError());
     }
     // the row hash of the adjacency tests (rows of degree <= 1024 many per
@@ -1401,16 +1443,19 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     // built on a side stream (it reads only the finished rows) and joined back
     // before returning: the rows of degree <= 1024 beside the reverse sort,
     // the longer ones beside the weights pass, so that each of the two
-    // shares the GPU with a part of the build
+    // shares the GPU with a part of the build.  Small graphs build it in line:
+    // the forks cost more than kernels of a few microseconds gain.
+    const bool beside = slots >= kBesideSlots;
     hipStream_t hside[2];
     PM_HIP(side_streams(hside));
-    Fork hfork(s, hside, 1);
+    Fork hfork(s, hside, beside ? 1 : 0);
     PM_HIP(hfork.status);
+    hipStream_t hs = beside ? hside[0] : s;
     // row classes 0, 5..8: degree above 0, 1024, 4096, 8192, 16384
     const int64_t hrows[5] = {cls[0], cls[5], cls[6], cls[7], cls[8]};
     const int64_t hslot_at[5] = {cls[kRowClasses + 1 + 0], cls[kRowClasses + 1 + 5], cls[kRowClasses + 1 + 6],
                                  cls[kRowClasses + 1 + 7], cls[kRowClasses + 1 + 8]};
-    PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hside[0], kRowHashSmall));
+    PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hs, kRowHashSmall));
 
     uint32_t *ka, *kb, *vfree, *v2a;
     PM_TRY(tmp.get(&ka, ss));
@@ -1423,9 +1468,9 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     uint32_t *keys_unused, *rev;
     PM_TRY(radix_sort("reverse_sort", RadixKeys{g->col}, kb, vfree, ka, v2a, slots, vbits, rscr, s, &keys_unused,
                       &rev, false));
-    Fork hfork2(s, hside, 1);  // the side stream now also waits for the reverse sort
+    Fork hfork2(s, hside, beside ? 1 : 0);  // the side stream now also waits for the reverse sort
     PM_HIP(hfork2.status);
-    PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hside[0], kRowHashWide));
+    PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hs, kRowHashWide));
 
     // weights, their prefixes and the guide tables of the edge draws (nothing
     // below indexes memory through the weights until the checks are read back)
@@ -1459,9 +1504,14 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
                                slots, g->p_tau, g->p_lam, g->rec, sums, st);
             PM_HIP(hipGetLastError());
         }
-        PM_TRY((scan_launch<U64x2, 16>(SegIn{sums}, SegOut{g->seg_tau, g->seg_lam, nseg, &st->totals}, nseg,
-                                       PairSumOp(), U64x2{0, 0}, scr, s)));
-        hipLaunchKernelGGL(k_guide_setup, dim3(1), dim3(1), 0, s, st, slots, g->guide_tau, g->guide_lam);
+        const SegOut seg_out{g->seg_tau, g->seg_lam, nseg, &st->totals};
+        if (nseg <= kOneBlockScan) {
+            hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, s, SegIn{sums}, seg_out, nseg, st, slots,
+                               g->guide_tau, g->guide_lam);
+        } else {
+            PM_TRY((scan_launch<U64x2, 16>(SegIn{sums}, seg_out, nseg, PairSumOp(), U64x2{0, 0}, scr, s)));
+            hipLaunchKernelGGL(k_guide_setup, dim3(1), dim3(1), 0, s, st, slots, g->guide_tau, g->guide_lam);
+        }
         PM_HIP(hipGetLastError());
         {
             ProfScope pg("weights.guide", s);
@@ -1470,23 +1520,18 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
                                (uint32_t)long_cap, st);
             PM_HIP(hipGetLastError());
         }
-        const unsigned gl = (unsigned)std::min<uint64_t>(long_cap, 2048);
-        hipLaunchKernelGGL(k_guide_long, dim3(gl), dim3(kBlock), 0, s, g->p_tau, g->seg_tau, &st->shift_tau,
-                           g->guide_tau, long_tau, &st->nlong_tau, (uint32_t)long_cap, &st->err);
-        hipLaunchKernelGGL(k_guide_long, dim3(gl), dim3(kBlock), 0, s, g->p_lam, g->seg_lam, &st->shift_lam,
-                           g->guide_lam, long_lam, &st->nlong_lam, (uint32_t)long_cap, &st->err);
+        const GuideLong lt{g->p_tau, g->seg_tau, g->guide_tau, long_tau}, ll{g->p_lam, g->seg_lam, g->guide_lam, long_lam};
+        hipLaunchKernelGGL(k_guide_long, dim3((unsigned)std::min<uint64_t>(long_cap, 2048), 2), dim3(kBlock), 0, s, lt,
+                           ll, (uint32_t)long_cap, st);
         PM_HIP(hipGetLastError());
     }
-    if (n > 0) {
-        hipLaunchKernelGGL(k_n1, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, g->deg, n, st);
-        PM_HIP(hipGetLastError());
-    }
-    PM_HIP(hipMemcpyAsync(&hst, st, sizeof(hst), hipMemcpyDeviceToHost, s));
-    PM_HIP(hipStreamSynchronize(s));
+    PM_HIP(hfork2.join());
+    PM_HIP(hfork.join());
+    PM_HIP(slot.read_back(&hst, st, sizeof(hst), s));
     // the scan writes its totals with the last segment offsets (seg[nseg]);
     // both stay 0 for an empty graph
     const uint64_t R[2] = {hst.totals.a, hst.totals.b};
-    if (hst.err & ERR_ASYM) {
+    if (hst.err & (ERR_RANGE | ERR_LOOP | ERR_ORDER | ERR_ASYM)) {
         set_error(err_text(hst.err));
         return PM_EGRAPH;
     }
@@ -1505,7 +1550,7 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     g->R_tau = R[0];
     g->R_lam = R[1];
     g->N1 = hst.n1_lo;
-    g->isolated = (int64_t)hst.isolated;
+    g->isolated = (int64_t)hst.cls[0].rows;
     if (g->R_tau) {
         g->shift_tau = hst.shift_tau;
         g->nb_tau = ((g->R_tau - 1) >> g->shift_tau) + 1;
@@ -1515,9 +1560,6 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         g->nb_lam = ((g->R_lam - 1) >> g->shift_lam) + 1;
     }
 
-    PM_HIP(hfork2.join());
-    PM_HIP(hfork.join());
-    PM_HIP(hipStreamSynchronize(s));
     guard.g = nullptr;
     *out = g;
     return PM_OK;

@@ -695,40 +695,6 @@ pm_status check_device(const pm_graph *g)
     return PM_OK;
 }
 
-// Pinned host memory for the tallies of kHostSlots calls at a time, one block
-// for the life of the process (portable: every device writes it).  A call
-// that finds no free slot, or no pinned memory, takes device memory and copies.
-struct HostTallies {
-    static constexpr int kSlots = 32;
-    std::mutex mu;
-    bool tried = false;
-    uint64_t *base = nullptr;
-    uint32_t used = 0;  // one bit per slot
-
-    uint64_t *take()
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        if (!tried) {
-            tried = true;
-            void *q = nullptr;
-            if (hipHostMalloc(&q, sizeof(uint64_t) * 2 * PM_NUM_TALLIES * kSlots, hipHostMallocPortable) == hipSuccess)
-                base = (uint64_t *)q;
-            else
-                (void)hipGetLastError();
-        }
-        if (!base || used == 0xFFFFFFFFu) return nullptr;
-        const int i = __builtin_ctz(~used);
-        used |= 1u << i;
-        return base + (size_t)i * 2 * PM_NUM_TALLIES;
-    }
-    void give(uint64_t *p)
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        used &= ~(1u << (int)((p - base) / (2 * PM_NUM_TALLIES)));
-    }
-};
-static HostTallies g_host_tallies;
-
 // Run both samplers of one graph through `run`, which fills 2 x PM_NUM_TALLIES
 // device tallies, with 2 x kMaxTallyParts rows of scratch -- or, when its last
 // step is one kernel's plain stores, `pinned` (if not null) instead, setting
@@ -750,27 +716,24 @@ pm_status count_with(const pm_graph *g, const pm_params *p, pm_result *out, hipS
         return PM_EINVAL;
     }
     PM_TRY(check_device(g));
-    uint64_t *t = nullptr, host[2 * PM_NUM_TALLIES], *pinned = g_host_tallies.take();
-    pm_status st = dev_alloc((void **)&t, 2 * (kMaxTallyParts + 1) * PM_NUM_TALLIES * sizeof(uint64_t), s);
-    if (st == PM_OK) {
-        bool placed = false;
-        st = run(g, p, t, t + 2 * PM_NUM_TALLIES, pinned, &placed, s);
-        hipError_t e = hipSuccess;
-        if (st == PM_OK && !placed)
-            e = hipMemcpyAsync(pinned ? pinned : host, t, sizeof(host), hipMemcpyDeviceToHost, s);
-        // also after a failure: a slot is given back only when nothing writes it
-        const hipError_t w = hipStreamSynchronize(s);
-        if (e == hipSuccess) e = w;
-        if (st == PM_OK && e != hipSuccess) {
-            set_error(std::string("pm_count: ") + hipGetErrorString(e));
-            st = PM_EDEVICE;
-        }
-        dev_free(t, s);
+    uint64_t *t = nullptr, host[2 * PM_NUM_TALLIES];
+    PM_TRY(dev_alloc((void **)&t, 2 * (kMaxTallyParts + 1) * PM_NUM_TALLIES * sizeof(uint64_t), s));
+    HostSlot slot;
+    bool placed = false;
+    pm_status st = run(g, p, t, t + 2 * PM_NUM_TALLIES, (uint64_t *)slot.p, &placed, s);
+    hipError_t e;
+    if (st == PM_OK && !placed) {
+        e = slot.read_back(host, t, sizeof(host), s);
+    } else {
+        // (also after a failure: the slot is given back when nothing writes it)
+        e = hipStreamSynchronize(s);
+        if (placed) std::memcpy(host, slot.p, sizeof(host));
     }
-    if (pinned) {
-        std::memcpy(host, pinned, sizeof(host));
-        g_host_tallies.give(pinned);
+    if (st == PM_OK && e != hipSuccess) {
+        set_error(std::string("pm_count: ") + hipGetErrorString(e));
+        st = PM_EDEVICE;
     }
+    dev_free(t, s);
     if (st != PM_OK) return st;
     return finalize(host, host + PM_NUM_TALLIES, g->R_tau / 2, g->R_lam / 2, g->N1, p->k_path, p->k_cent, p->delta,
                     out);

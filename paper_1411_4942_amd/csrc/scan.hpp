@@ -175,6 +175,48 @@ __global__ __launch_bounds__(kBlock) void scan_apply_kernel(In in, Out out, int6
     }
 }
 
+// The whole scan by one block of 1024 threads (few elements: one launch
+// instead of three).  Returns the total, in every thread.
+template <typename T, typename Op, typename In, typename Out>
+__device__ __forceinline__ T scan_one_block(In in, Out out, int64_t N, Op op, T identity)
+{
+    constexpr int kT = 1024, kPer = sizeof(T) > 8 ? 4 : 8, kW = kT / kWave;
+    __shared__ T s_wave[kW];
+    const int w = threadIdx.x / kWave, lane = lane_id();
+    T carry = identity;
+    for (int64_t base = 0; base < N; base += (int64_t)kT * kPer) {
+        // wave w: kPer rows of 64, in order
+        const int64_t w0 = base + (int64_t)w * kWave * kPer;
+        T v[kPer], run = identity;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int64_t idx = w0 + i * kWave + lane;
+            v[i] = idx < N ? in(idx) : identity;
+        }
+        T incl[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            incl[i] = op(run, wave_inclusive(v[i], op, identity));
+            run = shfl_idx_t(incl[i], kWave - 1);
+        }
+        if (lane == 0) s_wave[w] = run;
+        __syncthreads();
+        T pre = carry, all = identity;
+        for (int i = 0; i < kW; ++i) {
+            if (i < w) pre = op(pre, s_wave[i]);
+            all = op(all, s_wave[i]);
+        }
+        carry = op(carry, all);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int64_t idx = w0 + i * kWave + lane;
+            if (idx < N) out(idx, op(pre, incl[i]), v[i]);
+        }
+        __syncthreads();  // s_wave is written again in the next round
+    }
+    return carry;
+}
+
 // Scratch for one scan of N elements.
 template <typename T>
 struct ScanScratch {

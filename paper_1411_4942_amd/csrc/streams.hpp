@@ -4,12 +4,31 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+
 namespace pm {
 
 // Two streams per device (default priority, non-blocking), created on first
 // use on the current device and kept for the life of the process.  The row
 // build runs its classes of long rows on them beside the others.
 hipError_t side_streams(hipStream_t out[2]);
+
+// Pinned host memory for what a call reads back: kSlots slots of kBytes, one
+// allocation for the life of the process (portable: any device writes it).
+// A call takes a slot for its duration; `p` is null when none is free or
+// there is no pinned memory, and the caller then copies to pageable memory.
+// Give a slot back only when nothing on a device writes it any more.
+struct HostSlot {
+    static constexpr int kSlots = 32;
+    static constexpr size_t kBytes = 2048;
+    void *p;
+    HostSlot();
+    ~HostSlot();
+    HostSlot(const HostSlot &) = delete;
+    HostSlot &operator=(const HostSlot &) = delete;
+    // `bytes` of device memory to dst, after everything on s; waits for s
+    hipError_t read_back(void *dst, const void *dev, size_t bytes, hipStream_t s);
+};
 
 // Fork-join on side streams: on construction the side streams wait for
 // everything enqueued on s so far; join() makes s wait for everything
@@ -22,8 +41,9 @@ struct Fork {
     bool joined = false;
     hipError_t status = hipSuccess;
 
-    Fork(hipStream_t s_, hipStream_t *side_, int k_) : s(s_), side(side_), k(k_)
+    Fork(hipStream_t s_, hipStream_t *side_, int k_) : s(s_), side(side_), k(k_), joined(k_ == 0)
     {
+        if (k == 0) return;
         hipEvent_t e = nullptr;
         status = hipEventCreateWithFlags(&e, hipEventDisableTiming);
         if (status == hipSuccess) status = hipEventRecord(e, s);
