@@ -318,9 +318,12 @@ pm_status pm_count_batch(const pm_graph *const *graphs, const pm_params *params,
 
 /* A server owns registered graphs, prepares them on the device when a
  * request needs them (and keeps them resident within an HBM budget), and
- * runs requests in steps: each step is one persistent launch over work tiles
- * of every active request, so requests that arrive while others run are
- * admitted between steps and share the device with them.  A request either
+ * runs requests in steps: each step samples a chunk of every active request,
+ * in draw order from the samples of pm_set_draw_order on (with at most 0.3 GB
+ * of buffers beside the HBM budget, kept until pm_server_destroy; without
+ * memory for them in id order), else as one persistent launch over work
+ * tiles.  Requests that arrive while others run are admitted between steps
+ * and share the device with them.  A request either
  * gives its sample budgets or asks for a relative error: then its first
  * k_pilot ids per sampler are a pilot from which k is sized with
  * Corollary 5.3 (pm_samples_for_request) and the ids [k_pilot, k) follow.
@@ -336,7 +339,7 @@ typedef struct {
     uint64_t step_samples;   /* samples per step shared by the active requests (0: 2^25) */
     uint64_t k_pilot;        /* pilot ids per sampler (0: 65536) */
     uint64_t k_max;          /* cap on a sized budget, per sampler (0: 2e9) */
-    int32_t samples_per_tile;  /* work tile (0: 4096) */
+    int32_t samples_per_tile;  /* work tile of an id-order step (0: 4096) */
     int32_t blocks_per_cu;     /* resident blocks per compute unit (0: 4) */
 } pm_server_cfg;
 
@@ -448,8 +451,9 @@ pm_status pm_samples_for_error(double rel_err, double delta, double alpha, uint6
  * on the shape.  Default 1 and 4 (the fastest measured on MI355X). */
 pm_status pm_set_sampler_shape(int32_t samples_per_lane, int32_t blocks_per_cu);
 
-/* Draw-ordered sampling in pm_count, pm_sample_async and pm_count_alias
- * (this process; on by default).  When a sampler draws at least min_samples
+/* Draw-ordered sampling in pm_count, pm_sample_async, pm_count_alias and a
+ * server's steps (this process; on by default; a server's step sorts the
+ * samples of all its requests together, by graph, sampler and draw).  When a sampler draws at least min_samples
  * samples (0: the default 2^21, about where the sort starts to pay on
  * MI355X), their ids are first sorted, in chunks of 2^24, by the top 24 bits
  * of each sample's first draw (r of Algorithm 1 step 2 / Algorithm 3 step 2,

@@ -220,7 +220,8 @@ __device__ __forceinline__ uint32_t sample_class_wave(const SamplerView &g, uint
     return cls;
 }
 
-// Draw-ordered sampling (pm_count, pm_sample_async, pm_count_alias): for at
+// Draw-ordered sampling (pm_count, pm_sample_async, pm_count_alias, and over
+// many requests together step.hpp): for at
 // least draw_order_min() samples of one sampler, ids are sorted in chunks of
 // kSortedChunk by the top kDrawKeyBits bits of their first draw before they
 // run.  Measured on MI355X the sort pays from about 2M samples, for graphs

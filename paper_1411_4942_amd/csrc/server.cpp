@@ -1,8 +1,8 @@
 // Served mode: a request loop with continuous batching.
 //
-// One worker thread per server runs steps.  A step is one launch of the
-// persistent tile kernel over a chunk of every active request's remaining
-// ids; while it runs on the step stream the worker admits queued requests
+// One worker thread per server runs steps.  A step samples a chunk of every
+// active request's remaining ids, draw-ordered (step.hpp) or with one launch
+// of the persistent tile kernel; while it runs on the step stream the worker admits queued requests
 // (first come, first served) and prepares the graphs they need on a second
 // stream, so preparation overlaps sampling and new requests join the next
 // step.  Admission needs a free slot and the graph resident: a graph that is
@@ -26,7 +26,7 @@
 #include <unordered_map>
 #include <vector>
 
-#include "batch.hpp"
+#include "step.hpp"
 
 namespace pm {
 
@@ -112,6 +112,7 @@ struct pm_server {
     pm::BatchCtl *d_ctl = nullptr, *h_ctl = nullptr;
     uint64_t *d_tallies = nullptr, *h_tallies = nullptr;
     unsigned max_blocks = 1;
+    pm::StepRunner order;  // draw-ordered steps
 };
 
 namespace pm {
@@ -327,7 +328,8 @@ pm_status grow_tiles(pm_server *S, uint32_t need)
 
 // Cut this step's chunks: the pilot whole, otherwise an equal share of
 // step_samples per (request, sampler) with work left, in whole tiles.
-pm_status build_step(pm_server *S, uint32_t *ntiles)
+// *samples receives their sum.
+void cut_chunks(pm_server *S, uint64_t *samples)
 {
     const uint64_t tile = (uint64_t)S->cfg.samples_per_tile;
     uint64_t nwork = 0;
@@ -336,13 +338,22 @@ pm_status build_step(pm_server *S, uint32_t *ntiles)
             if (r->next[tag] < target_of(S, r, tag)) ++nwork;
     uint64_t share = S->cfg.step_samples / std::max<uint64_t>(nwork, 1);
     share = std::max<uint64_t>(tile, (share + tile - 1) / tile * tile);
-    uint64_t need = 0;
+    *samples = 0;
     for (SrvReq *r : S->active)
         for (int tag = 0; tag < 2; ++tag) {
             const uint64_t rem = target_of(S, r, tag) - std::min(r->next[tag], target_of(S, r, tag));
             r->chunk[tag] = r->sized ? std::min(rem, share) : rem;
-            need += (r->chunk[tag] + tile - 1) / tile;
+            *samples += r->chunk[tag];
         }
+}
+
+// The step's tile table (id-order steps).
+pm_status fill_tiles(pm_server *S, uint32_t *ntiles)
+{
+    const uint64_t tile = (uint64_t)S->cfg.samples_per_tile;
+    uint64_t need = 0;
+    for (SrvReq *r : S->active)
+        for (int tag = 0; tag < 2; ++tag) need += (r->chunk[tag] + tile - 1) / tile;
     if (need > 0xFFFFFFF0ull) {
         set_error("server: step too large");
         return PM_EINVAL;
@@ -364,18 +375,40 @@ pm_status build_step(pm_server *S, uint32_t *ntiles)
     return PM_OK;
 }
 
-pm_status launch_step(pm_server *S, uint32_t ntiles)
+// Enqueue one step over the active requests' chunks; *launched is false when
+// none has work.
+pm_status launch_step(pm_server *S, bool *launched)
 {
-    S->h_ctl->ntiles = ntiles;
-    S->h_ctl->cursor = 0;
-    S->h_ctl->nlists = 0;  // one cursor
+    uint64_t samples = 0;
+    cut_chunks(S, &samples);
+    *launched = samples > 0;
+    if (!*launched) return PM_OK;
     const size_t tb = sizeof(uint64_t) * (size_t)S->cfg.max_active * 2 * PM_NUM_TALLIES;
     PM_HIP(hipEventRecord(S->ev_a, S->s_step));
-    PM_HIP(hipMemcpyAsync(S->d_tiles, S->h_tiles, sizeof(BatchTile) * ntiles, hipMemcpyHostToDevice, S->s_step));
-    PM_HIP(hipMemcpyAsync(S->d_ctl, S->h_ctl, sizeof(BatchCtl), hipMemcpyHostToDevice, S->s_step));
-    PM_TRY(fill_async<uint64_t>(S->d_tallies, 0ull, (int64_t)S->cfg.max_active * 2 * PM_NUM_TALLIES, S->s_step));
-    const unsigned blocks = (unsigned)std::max<uint32_t>(1, std::min<uint32_t>(S->max_blocks, ntiles));
-    PM_TRY(launch_tiles(S->d_graphs, S->d_tiles, S->d_ctl, S->d_tallies, blocks, S->s_step));
+    bool ordered = false;
+    std::vector<StepItem> items;
+    items.reserve(2 * S->active.size());
+    for (SrvReq *r : S->active) {
+        const pm_graph *g = S->graphs[r->rq.graph].g;
+        for (int tag = 0; tag < 2; ++tag)
+            if (r->chunk[tag])
+                items.push_back({r->rq.graph, (uint32_t)tag, (uint32_t)r->slot, r->next[tag], r->chunk[tag], r->rq.seed,
+                                 tag == 0 ? g->R_tau : g->R_lam});
+    }
+    PM_TRY(S->order.run(S->d_graphs, items, S->d_tallies, S->cfg.max_active, S->max_blocks, S->s_step,
+                        &ordered));
+    if (!ordered) {
+        uint32_t ntiles = 0;
+        PM_TRY(fill_tiles(S, &ntiles));
+        S->h_ctl->ntiles = ntiles;
+        S->h_ctl->cursor = 0;
+        S->h_ctl->nlists = 0;  // one cursor
+        PM_HIP(hipMemcpyAsync(S->d_tiles, S->h_tiles, sizeof(BatchTile) * ntiles, hipMemcpyHostToDevice, S->s_step));
+        PM_HIP(hipMemcpyAsync(S->d_ctl, S->h_ctl, sizeof(BatchCtl), hipMemcpyHostToDevice, S->s_step));
+        PM_TRY(fill_async<uint64_t>(S->d_tallies, 0ull, (int64_t)S->cfg.max_active * 2 * PM_NUM_TALLIES, S->s_step));
+        const unsigned blocks = (unsigned)std::max<uint32_t>(1, std::min<uint32_t>(S->max_blocks, ntiles));
+        PM_TRY(launch_tiles(S->d_graphs, S->d_tiles, S->d_ctl, S->d_tallies, blocks, S->s_step));
+    }
     PM_HIP(hipMemcpyAsync(S->h_tallies, S->d_tallies, tb, hipMemcpyDeviceToHost, S->s_step));
     PM_HIP(hipEventRecord(S->ev_b, S->s_step));
     return PM_OK;
@@ -412,13 +445,10 @@ void worker_main(pm_server *S)
         }
         bool launched = false;
         if (!S->active.empty()) {
-            uint32_t ntiles = 0;
-            pm_status st = build_step(S, &ntiles);
-            if (st == PM_OK && ntiles > 0) st = launch_step(S, ntiles);
+            const pm_status st = launch_step(S, &launched);
             if (st != PM_OK) {
+                launched = false;
                 fail_active(S, st, last_error_text());
-            } else {
-                launched = ntiles > 0;
             }
         }
         // admissions (and graph preparations) overlap the step in flight
@@ -496,6 +526,7 @@ void server_free(pm_server *S)
     dev_free(S->d_tiles, S->s_step);
     dev_free(S->d_ctl, S->s_step);
     dev_free(S->d_tallies, S->s_step);
+    S->order.free(S->s_step);
     if (S->h_graphs) (void)hipHostFree(S->h_graphs);
     if (S->h_tiles) (void)hipHostFree(S->h_tiles);
     if (S->h_ctl) (void)hipHostFree(S->h_ctl);

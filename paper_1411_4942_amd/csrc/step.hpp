@@ -1,0 +1,68 @@
+// Draw-ordered steps of the batched and the served paths: the samples of many
+// graphs and requests, run graph by graph in the order of their draws.
+#pragma once
+
+#include <vector>
+
+#include "batch.hpp"
+
+namespace pm {
+
+// The samples first, first + 1, ..., first + count - 1 of one sampler of one
+// graph (weight R > 0), counted into tally slot `slot`.
+struct StepItem {
+    uint32_t graph;
+    uint32_t tag;  // 0 3-path sampler, 1 centered sampler
+    uint32_t slot;
+    uint64_t first, count, seed, R;
+};
+
+// A step is run in parts of at most kSortedChunk samples, each a sequence of
+// chunks laid end to end: positions [start, next chunk's start) are the
+// samples first, first + 1, ... of one item.  The chunks of one graph and
+// sampler follow each other and form a group.  Both tables end with a
+// sentinel that holds the end positions.
+struct StepChunk {
+    uint64_t first, seed;
+    uint32_t start;
+    uint32_t slot;
+    uint32_t group;
+    uint32_t pad;
+};
+
+struct StepGroup {
+    double scale;     // (samples of the group) / (total weight of its sampler)
+    uint32_t begin;   // first position
+    uint32_t chunk0;  // first chunk
+    uint32_t graph;
+    uint32_t tag;
+};
+
+constexpr uint32_t kStepChunks = 512;  // chunks of a part, at most (their counts live in LDS: 16 KiB)
+constexpr unsigned kStepBlocks = 2048;  // blocks of a launch, at most (more would not be resident)
+
+// Runs draw-ordered steps on one stream, with buffers grown to the largest
+// step seen (at most those of a part of kSortedChunk samples).  One step at a
+// time: the caller has waited for the step before.
+class StepRunner {
+public:
+    // Enqueue the items' samples: tallies[0, slots * 16) receive their counts
+    // (slot * 16 + tag * 8 + c; zero elsewhere).  No two items share a slot
+    // and a sampler.  *done is false, and nothing is enqueued, where the step
+    // is left to the id order: fewer than draw_order_min() samples, draw
+    // order off, too many small items, or no memory.
+    pm_status run(const BatchGraph *graphs, std::vector<StepItem> &items, uint64_t *tallies, int64_t slots,
+                  unsigned blocks, hipStream_t s, bool *done);
+    void free(hipStream_t s);
+
+private:
+    bool grow(size_t table_bytes, uint64_t part, hipStream_t s);
+
+    char *d_tables = nullptr, *h_tables = nullptr;  // the parts' tables; h_ pinned
+    size_t table_cap = 0;
+    char *d_order = nullptr;  // the sort's buffers, then the blocks' counts
+    uint64_t order_cap = 0;   // positions d_order holds
+    bool off = false;         // no memory for them
+};
+
+}  // namespace pm
