@@ -288,9 +288,12 @@ typedef struct pm_batch pm_batch;
  * id).  The work is a table of tiles (graph, sampler, first id, count, seed)
  * consumed by one persistent kernel; the whole run (table upload, tally
  * reset, kernel, tally download) is captured once as a HIP graph on an
- * internal stream and replayed by pm_batch_run.  The batch keeps pointers to
- * the graphs: destroy the batch before them.  Errors: PM_EINVAL (null,
- * count <= 0, a graph on another device, k_path = k_cent = 0, delta outside
+ * internal stream and replayed by pm_batch_run.  Runs of pm_set_draw_order's
+ * samples or more are launched in draw order instead, the samples of all the
+ * graphs sorted together (with at most 0.3 GB of buffers, kept until
+ * pm_batch_destroy; without memory for them the graph is replayed).  The
+ * batch keeps pointers to the graphs: destroy the batch before them.
+ * Errors: PM_EINVAL (null, count <= 0, a graph on another device, k_path = k_cent = 0, delta outside
  * (0,1), bad tune), PM_ENOMEM, PM_EDEVICE. */
 pm_status pm_batch_create(const pm_graph *const *graphs, const pm_params *params, int32_t count, const pm_tune *tune,
                           void *stream, pm_batch **out);
@@ -301,7 +304,7 @@ pm_status pm_batch_create(const pm_graph *const *graphs, const pm_params *params
  * tiles of min(1024, the requested tile size) samples). */
 pm_status pm_batch_set_params(pm_batch *b, const pm_params *params);
 
-/* Replay the batch after the work already on `stream`; out[count] receives
+/* Run the batch after the work already on `stream`; out[count] receives
  * each graph's result.  Returns when the results are on the host. */
 pm_status pm_batch_run(pm_batch *b, pm_result *out, void *stream);
 
@@ -340,7 +343,7 @@ typedef struct {
     uint64_t k_pilot;        /* pilot ids per sampler (0: 65536) */
     uint64_t k_max;          /* cap on a sized budget, per sampler (0: 2e9) */
     int32_t samples_per_tile;  /* work tile of an id-order step (0: 4096) */
-    int32_t blocks_per_cu;     /* resident blocks per compute unit (0: 4) */
+    int32_t blocks_per_cu;     /* resident blocks per compute unit (0: 4, 6 in draw order) */
 } pm_server_cfg;
 
 typedef struct {
@@ -451,10 +454,11 @@ pm_status pm_samples_for_error(double rel_err, double delta, double alpha, uint6
  * on the shape.  Default 1 and 4 (the fastest measured on MI355X). */
 pm_status pm_set_sampler_shape(int32_t samples_per_lane, int32_t blocks_per_cu);
 
-/* Draw-ordered sampling in pm_count, pm_sample_async, pm_count_alias and a
- * server's steps (this process; on by default; a server's step sorts the
- * samples of all its requests together, by graph, sampler and draw).  When a sampler draws at least min_samples
- * samples (0: the default 2^21, about where the sort starts to pay on
+/* Draw-ordered sampling in pm_count, pm_sample_async, pm_count_alias, a batch's
+ * runs and a server's steps (this process; on by default; the last two sort
+ * the samples of all their graphs and requests together, by graph, sampler
+ * and draw).  When a sampler (for the last two: all together) draws at least
+ * min_samples samples (0: the default 2^21, about where the sort starts to pay on
  * MI355X), their ids are first sorted, in chunks of 2^24, by the top 24 bits
  * of each sample's first draw (r of Algorithm 1 step 2 / Algorithm 3 step 2,
  * or the alias bucket), so that neighbouring lanes read neighbouring parts of

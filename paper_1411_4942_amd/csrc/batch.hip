@@ -8,6 +8,10 @@
 // Samples depend only on (seed, sampler, id): a graph's tallies equal those
 // of its own pm_count with the same parameters, whatever the tiling.
 //
+// Runs of pm_set_draw_order's samples or more go in draw order instead
+// (step.hpp), launched rather than replayed: the parts and their sizes follow
+// the budgets.
+//
 // The replayed graph is: tile table and control block host -> device (from
 // pinned buffers, so a new table needs no recapture), tallies zeroed by a
 // kernel, the persistent kernel, tallies device -> host.
@@ -18,9 +22,9 @@
 #include <new>
 #include <vector>
 
-#include "batch.hpp"
 #include "profile.hpp"
 #include "sampler.hpp"
+#include "step.hpp"
 
 namespace pm {
 
@@ -108,6 +112,9 @@ struct pm_batch {
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    pm::StepRunner order;  // draw-ordered runs
+    std::vector<pm::StepItem> items;
+    unsigned order_blocks = 0;
 };
 
 namespace pm {
@@ -201,6 +208,7 @@ void batch_free(pm_batch *b)
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
+    b->order.free(b->stream);
     dev_free(b->d_graphs, b->stream);
     dev_free(b->d_tiles, b->stream);
     dev_free(b->d_ctl, b->stream);
@@ -242,6 +250,16 @@ pm_status set_shape(pm_batch *b, const pm_tune &t)
     }
     b->tune = t;
     b->ntiles = fill_tiles(b, (uint32_t)t.samples_per_tile);
+    b->items.clear();
+    for (int32_t i = 0; i < b->count; ++i)
+        for (int tag = 0; tag < 2; ++tag) {
+            const pm_graph *g = b->graphs[i];
+            const pm_params &p = b->params[i];
+            if (const uint64_t k = budget(g, p, tag))
+                b->items.push_back({(uint32_t)i, (uint32_t)tag, (uint32_t)i,
+                                    tag == 0 ? p.first_id_path : p.first_id_cent, k, p.seed,
+                                    tag == 0 ? g->R_tau : g->R_lam});
+        }
     b->h_ctl->ntiles = b->ntiles;
     b->h_ctl->cursor = 0;
     const uint64_t cap = (uint64_t)sampler_cu_count(b->device) * (uint64_t)t.blocks_per_cu;
@@ -409,6 +427,10 @@ pm_status batch_create(const pm_graph *const *graphs, const pm_params *params, i
     } else {
         PM_TRY(autotune(b, &t));
     }
+    // the shapes tried are those of the tile kernel: without a tune the
+    // draw-ordered runs take the samplers' own
+    b->order_blocks = (unsigned)sampler_cu_count(b->device) *
+                      (unsigned)(tune && tune->samples_per_tile > 0 ? t.blocks_per_cu : kStepBlocksPerCu);
     PM_TRY(set_shape(b, t));
     PM_TRY(capture(b));
     guard.b = nullptr;
@@ -448,7 +470,13 @@ pm_status batch_run(pm_batch *b, pm_result *out, hipStream_t user_stream)
     PM_HIP(hipStreamWaitEvent(b->stream, b->ev_in, 0));
     {
         ProfScope prof("sample_batch", b->stream);
-        PM_HIP(hipGraphLaunch(b->exec, b->stream));
+        bool ordered = false;
+        PM_TRY(b->order.run(b->d_graphs, b->items, b->d_tallies, b->count, b->order_blocks, b->stream, &ordered));
+        if (ordered)
+            PM_HIP(hipMemcpyAsync(b->h_tallies, b->d_tallies, sizeof(uint64_t) * b->count * 2 * PM_NUM_TALLIES,
+                                  hipMemcpyDeviceToHost, b->stream));
+        else
+            PM_HIP(hipGraphLaunch(b->exec, b->stream));
     }
     PM_HIP(hipStreamSynchronize(b->stream));
     for (int32_t i = 0; i < b->count; ++i) {

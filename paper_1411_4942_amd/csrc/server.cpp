@@ -111,7 +111,8 @@ struct pm_server {
     uint32_t tile_cap = 0;
     pm::BatchCtl *d_ctl = nullptr, *h_ctl = nullptr;
     uint64_t *d_tallies = nullptr, *h_tallies = nullptr;
-    unsigned max_blocks = 1;
+    unsigned max_blocks = 1;    // of an id-order step
+    unsigned order_blocks = 1;  // of a draw-ordered one
     pm::StepRunner order;  // draw-ordered steps
 };
 
@@ -395,7 +396,7 @@ pm_status launch_step(pm_server *S, bool *launched)
                 items.push_back({r->rq.graph, (uint32_t)tag, (uint32_t)r->slot, r->next[tag], r->chunk[tag], r->rq.seed,
                                  tag == 0 ? g->R_tau : g->R_lam});
     }
-    PM_TRY(S->order.run(S->d_graphs, items, S->d_tallies, S->cfg.max_active, S->max_blocks, S->s_step,
+    PM_TRY(S->order.run(S->d_graphs, items, S->d_tallies, S->cfg.max_active, S->order_blocks, S->s_step,
                         &ordered));
     if (!ordered) {
         uint32_t ntiles = 0;
@@ -566,6 +567,7 @@ pm_status server_create(const pm_server_cfg *cfg_in, pm_server **out)
     if (c.k_pilot == 0) c.k_pilot = 65536;
     if (c.k_max == 0) c.k_max = 2000000000ull;
     if (c.samples_per_tile == 0) c.samples_per_tile = 4096;
+    const int order_blocks = c.blocks_per_cu ? c.blocks_per_cu : kStepBlocksPerCu;
     if (c.blocks_per_cu == 0) c.blocks_per_cu = 4;
     if (c.k_max < c.k_pilot) {
         set_error("server: k_max below k_pilot");
@@ -604,6 +606,7 @@ pm_status server_create(const pm_server_cfg *cfg_in, pm_server **out)
     PM_TRY(grow_tiles(S, (uint32_t)std::min<uint64_t>(1u << 20, c.step_samples / c.samples_per_tile + 2 * c.max_active)));
     PM_HIP(hipStreamSynchronize(S->s_step));
     S->max_blocks = (unsigned)std::max(1, sampler_cu_count(S->device) * c.blocks_per_cu);
+    S->order_blocks = (unsigned)std::max(1, sampler_cu_count(S->device) * order_blocks);
     S->worker = std::thread(worker_main, S);
     guard.s = nullptr;
     *out = S;

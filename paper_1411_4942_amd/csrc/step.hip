@@ -4,8 +4,8 @@
 // random lines of this memory.  Sorted by (graph, sampler, draw) the samples
 // of all the requests on a graph sweep its slots once, together: 64 requests
 // of 1.0e8 samples in all on 12 graphs went from 13.2 to 8.3 ms of steps, 1.4
-// of them the sorts (4.1 ps a sample for the keys, 2.3 + 0.4 + 1.9 for the
-// rest) and the others 65 ps a sample.
+// of them the sorts and the others 65 ps a sample; 64 graphs at 2e5 + 2e5
+// samples from 2.82 to 2.34 ms a run.
 #include "step.hpp"
 
 #include <algorithm>

@@ -40,6 +40,11 @@ struct StepGroup {
 
 constexpr uint32_t kStepChunks = 512;  // chunks of a part, at most (their counts live in LDS: 16 KiB)
 constexpr unsigned kStepBlocks = 2048;  // blocks of a launch, at most (more would not be resident)
+// Blocks per compute unit where the caller sets none: 64 graphs of up to 2e6
+// edges at 2e5 + 2e5 samples each took 2.23, 2.10, 1.98 and 1.97 ms a run at
+// 4, 5, 6 and 7 (in id order more blocks hold more graphs in flight and are
+// slower: 13.8 ms at 4, 16.3 at 8, over the requests of step.hip).
+constexpr int kStepBlocksPerCu = 6;
 
 // Runs draw-ordered steps on one stream, with buffers grown to the largest
 // step seen (at most those of a part of kSortedChunk samples).  One step at a
