@@ -185,16 +185,26 @@ int sampler_cu_count(int dev)
     return cache[dev];
 }
 
+// Blocks per compute unit of a draw-ordered launch at the default shape: its
+// blocks sweep one window of the graph together, so more of them hide more
+// latency without holding more of the graph.  1e7 + 1e7 samples took 1.33,
+// 1.21, 1.16 and 1.33 ms at 4, 5, 6 and 7 blocks on 1e6 edges, 1.66, 1.60,
+// 1.57 and 1.87 on 1e7, 2.56, 2.50, 2.51 and 3.01 on 1.2e8.  In id order 4
+// stay best (2e6 + 2e6 on 1e7 edges: 0.65 ms at 4, 0.69 at 6, 0.75 at 7).
+constexpr unsigned kOrderBlocksPerCu = 6;
+
 // The process-wide settings as one call uses them (read once, so that a
 // setter on another thread cannot change them between its launches).
 struct SampleShape {
     int per_lane, mode;
-    unsigned cap;  // most blocks of a launch
+    unsigned cap;        // most blocks of an id-order launch
+    unsigned order_cap;  // most blocks of a draw-ordered one
     bool order;
     uint64_t order_min;
     explicit SampleShape(const pm_graph *g)
         : per_lane(g_samples_per_lane.load()), mode(g_search_mode.load()),
-          cap((unsigned)(sampler_cu_count(g->device) * g_blocks_per_cu.load())), order(draw_order_enabled()),
+          cap((unsigned)(sampler_cu_count(g->device) * g_blocks_per_cu.load())),
+          order_cap(cap == 4u * (unsigned)sampler_cu_count(g->device) ? cap / 4 * kOrderBlocksPerCu : cap), order(draw_order_enabled()),
           order_min(draw_order_min())
     {
     }
@@ -262,7 +272,7 @@ static pm_status sample_chunk(const SampleShape &sh, const SamplerView &v, bool 
                               uint64_t first, uint64_t kc, const uint32_t *ids, uint64_t *tally, uint64_t *parts,
                               hipStream_t s)
 {
-    const unsigned kb = chunk_blocks(kc, sh.cap);
+    const unsigned kb = chunk_blocks(kc, sh.order_cap);
     unsigned long long *t = (unsigned long long *)tally, *q = (unsigned long long *)parts;
     ProfScope pk(centered ? "sample_centered.sorted" : "sample_path.sorted", s);
     const int mode = sh.mode;
@@ -321,7 +331,7 @@ static pm_status launch_sorted(const SampleShape &sh, const SamplerView &v, bool
 }
 
 // One sampler's k samples from id `first`: into tally (device, added to), or
-// with `parts` (an id-order launch of sh.cap <= kMaxTallyParts), as *rows rows
+// with `parts` (an id-order launch, sh.cap <= kMaxTallyParts), as *rows rows
 // of parts.  Draw-ordered launches take their buffers from `fixed` when
 // given, else from the allocator.
 static pm_status launch_sampler(const SampleShape &sh, const pm_graph *g, bool centered, uint64_t seed,
@@ -474,8 +484,8 @@ static pm_status sample_pair_overlapped(const SampleShape &sh, const pm_graph *g
         // slows it by more than the join costs
         PM_HIP(fork.join());
     }
-    rows[0] = chunk_blocks(p->k_path, sh.cap);
-    rows[1] = chunk_blocks(p->k_cent, sh.cap);
+    rows[0] = chunk_blocks(p->k_path, sh.order_cap);
+    rows[1] = chunk_blocks(p->k_cent, sh.order_cap);
     {
         ProfScope prof("sample_path", s);
         PM_TRY(sample_chunk(sh, vp, false, p->seed, p->first_id_path, p->k_path, ids_p, tallies, parts[0], s));
@@ -534,7 +544,7 @@ static pm_status sample_into(const pm_graph *g, const pm_params *p, uint64_t *ta
     PM_TRY(check_device(g));
     const SampleShape sh(g);
     const bool pair = sh.one_chunk(g->R_tau, p->k_path) && sh.one_chunk(g->R_lam, p->k_cent);
-    if (sh.cap > kMaxTallyParts || std::max(p->k_path, p->k_cent) > kMaxLaunchSamples ||
+    if (std::max(sh.cap, sh.order_cap) > kMaxTallyParts || std::max(p->k_path, p->k_cent) > kMaxLaunchSamples ||
         (!pair && (sh.sorted(g->R_tau, p->k_path) || sh.sorted(g->R_lam, p->k_cent))))
         scratch = nullptr;
     if (!scratch) PM_TRY(fill_async<uint64_t>(tallies_dev, 0ull, 2 * PM_NUM_TALLIES, s));
