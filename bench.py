@@ -64,6 +64,8 @@ def rev_pass_bytes(n: int) -> float:
     passes = (bits + 10) // 11
     if passes == 1:
         return 8.0  # key read, value written
+    if passes == 2:
+        return 10.0  # keys pass between the two as 16 bits
     per = [12.0] + [16.0] * (passes - 2) + [12.0]
     return sum(per) / passes
 
@@ -766,9 +768,10 @@ def main():
         # per launch, averaged over the passes: the first reads no value (the
         # payload is the position: key 4 read, key 4 + value 4 written), the
         # middle ones read and write key + value (16), the last writes no key
-        # (key 4 + value 4 read, value 4 written)
+        # (key 4 + value 4 read, value 4 written); of two passes the second
+        # reads 2 bytes of key
         "reverse_sort.scatter": (rev_pass_bytes(info["n"]) * slots, "pm::radix_scatter"),
-        "reverse_sort.histogram": (4 * slots, "pm::radix_histogram"),
+        "reverse_sort.histogram": ((3 if rev_pass_bytes(info["n"]) == 10.0 else 4) * slots, "pm::radix_histogram"),
         # per slot: input column 4, its rank 4, column 4 and edge 8 written
         "build_rows": (20 * slots, "pm::k_rows_block"),
         # per slot: edge 8 + rev 4, both rows' 32-bit offset pairs 16, both
