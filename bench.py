@@ -772,11 +772,11 @@ def main():
         # reads 2 bytes of key
         "reverse_sort.scatter": (rev_pass_bytes(info["n"]) * slots, "pm::radix_scatter"),
         "reverse_sort.histogram": ((3 if rev_pass_bytes(info["n"]) == 10.0 else 4) * slots, "pm::radix_histogram"),
-        # per slot: input column 4, its rank 4, column 4 and edge 8 written
-        "build_rows": (20 * slots, "pm::k_rows_block"),
-        # per slot: edge 8 + rev 4, both rows' 32-bit offset pairs 16, both
+        # per slot: input column 4, its rank 4, column 4 written
+        "build_rows": (12 * slots, "pm::k_rows_block"),
+        # per slot: column 4 + rev 4, both rows' 32-bit offset pairs 16, both
         # segment prefixes written 16, the slot record written 16
-        "weights.reduce": (60 * slots, "pm::k_weights_reduce"),
+        "weights.reduce": (56 * slots, "pm::k_weights_reduce"),
         # per slot: its column read 4, two row-hash entries written 8
         "rowhash": (12 * slots, "pm::k_rowhash_small"),
         # per slot: both segment prefixes read 16, guide entries 2 (2m/4 buckets of 4 bytes per table)

@@ -187,11 +187,15 @@ struct DegIn {
     __device__ __forceinline__ uint64_t operator()(int64_t i) const { return d[i]; }
 };
 struct OffOut {
-    uint32_t *off;  // writes off[i+1] (below 2^32: the slot count is), and off[0]
-    __device__ __forceinline__ void operator()(int64_t i, uint64_t incl, uint64_t) const
+    uint32_t *off;      // writes off[i+1] (below 2^32: the slot count is), and off[0]
+    uint32_t *seg_row;  // the row that holds each prefix segment's first slot
+    uint64_t nseg;
+    __device__ __forceinline__ void operator()(int64_t i, uint64_t incl, uint64_t d) const
     {
         if (i == 0) off[0] = 0u;
         off[i + 1] = (uint32_t)incl;
+        for (uint64_t sg = (incl - d + kPrefixSeg - 1) / kPrefixSeg; sg * kPrefixSeg < incl && sg < nseg; ++sg)
+            seg_row[sg] = (uint32_t)i;
     }
 };
 
@@ -215,8 +219,8 @@ struct OffOut {
 //   degree > 32768        (the few hub rows, all at the end of the order)
 //                         chunks of 32768 sorted as the class above, then
 //                         merged within each row
-// Each class writes col, edge = row | col << 32, and ladder level 1 (every
-// 32nd column) at the row's final slots, and checks the input row (column
+// Each class writes col and ladder level 1 (every 32nd column) at the row's
+// final slots, and checks the input row (column
 // range, self-loop, strictly ascending).
 // ---------------------------------------------------------------------------
 
@@ -230,11 +234,10 @@ __device__ __forceinline__ uint32_t slot_checks(int64_t c, int64_t u, int64_t pr
     return e;
 }
 
-__device__ __forceinline__ void emit_slot(int64_t p, uint32_t row, uint32_t c, uint32_t *__restrict__ col,
-                                          uint64_t *__restrict__ edge, uint32_t *__restrict__ ladder1)
+__device__ __forceinline__ void emit_slot(int64_t p, uint32_t c, uint32_t *__restrict__ col,
+                                          uint32_t *__restrict__ ladder1)
 {
     col[p] = c;
-    edge[p] = (uint64_t)row | ((uint64_t)c << 32);
     if (ladder1 && (p & 31) == 0) ladder1[p >> 5] = c;
 }
 
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_group(const int64_t *__restrict
                                                        const int32_t *__restrict__ rank,
                                                        const uint32_t *__restrict__ off_new, int64_t n, int64_t r0,
                                                        int64_t r1, uint32_t *__restrict__ col,
-                                                       uint64_t *__restrict__ edge, uint32_t *__restrict__ ladder1,
+                                                       uint32_t *__restrict__ ladder1,
                                                        PrepStats *st)
 {
     static_assert(W == 16 || W == 64, "a quarter wave or a wave per row");
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_group(const int64_t *__restrict
             const bool up = (j & size) == 0, low = (j & stride) == 0;
             v = (up == low) ? (v < o ? v : o) : (v < o ? o : v);
         }
-    if (ok) emit_slot(off_new[i] + j, (uint32_t)i, v, col, edge, ladder1);
+    if (ok) emit_slot(off_new[i] + j, v, col, ladder1);
     if (err) atomicOr(&st->err, err);
 }
 
@@ -329,7 +332,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_bitonic(const int64_t *__restri
                                                          const int32_t *__restrict__ rank,
                                                          const uint32_t *__restrict__ off_new, int64_t n, int64_t r0,
                                                          int64_t r1, uint32_t *__restrict__ col,
-                                                         uint64_t *__restrict__ edge, uint32_t *__restrict__ ladder1,
+                                                         uint32_t *__restrict__ ladder1,
                                                          PrepStats *st)
 {
     static_assert(ITEMS == 2 || ITEMS == 4, "two or four keys per lane");
@@ -368,7 +371,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_bitonic(const int64_t *__restri
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const int e = lane * ITEMS + j;
-        if (e < d) emit_slot(dst + e, (uint32_t)i, k[j], col, edge, ladder1);
+        if (e < d) emit_slot(dst + e, k[j], col, ladder1);
     }
     if (err) atomicOr(&st->err, err);
 }
@@ -543,7 +546,7 @@ __global__ __launch_bounds__(THREADS) void k_rows_block(const int64_t *__restric
                                                         const int32_t *__restrict__ rank,
                                                         const uint32_t *__restrict__ off_new, int64_t n, int64_t r0,
                                                         int bits, uint32_t *__restrict__ col,
-                                                        uint64_t *__restrict__ edge, uint32_t *__restrict__ ladder1,
+                                                        uint32_t *__restrict__ ladder1,
                                                         PrepStats *st)
 {
     constexpr int CAP = THREADS * ITEMS;
@@ -563,7 +566,7 @@ __global__ __launch_bounds__(THREADS) void k_rows_block(const int64_t *__restric
     __syncthreads();
     const uint32_t *sorted = block_radix_lds<THREADS, ITEMS>(s_a, s_b, d, bits, s_cnt, s_tot);
     const int64_t dst = off_new[i];
-    for (int j = threadIdx.x; j < d; j += THREADS) emit_slot(dst + j, (uint32_t)i, sorted[j], col, edge, ladder1);
+    for (int j = threadIdx.x; j < d; j += THREADS) emit_slot(dst + j, sorted[j], col, ladder1);
     if (err) atomicOr(&st->err, err);
 }
 
@@ -577,7 +580,6 @@ __global__ __launch_bounds__(THREADS) void k_rows_block_reg(const int64_t *__res
                                                             const int32_t *__restrict__ rank,
                                                             const uint32_t *__restrict__ off_new, int64_t n,
                                                             int64_t r0, int bits, uint32_t *__restrict__ col,
-                                                            uint64_t *__restrict__ edge,
                                                             uint32_t *__restrict__ ladder1, PrepStats *st)
 {
     constexpr int CAP = THREADS * ITEMS;
@@ -604,7 +606,7 @@ __global__ __launch_bounds__(THREADS) void k_rows_block_reg(const int64_t *__res
     // the first pass writes s_buf only after its own barriers
     block_radix_reg<THREADS, ITEMS>(key, s_buf, d, bits, s_cnt, s_tot);
     const int64_t dst = off_new[i];
-    for (int j = threadIdx.x; j < d; j += THREADS) emit_slot(dst + j, (uint32_t)i, s_buf[j], col, edge, ladder1);
+    for (int j = threadIdx.x; j < d; j += THREADS) emit_slot(dst + j, s_buf[j], col, ladder1);
     if (err) atomicOr(&st->err, err);
 }
 
@@ -718,7 +720,7 @@ __global__ __launch_bounds__(THREADS) void k_hub_chunks(const int64_t *__restric
 // sorted runs [s, s + L) and [s + L, s + 2L) (s = the row's start plus a
 // multiple of 2L, both cut at the row's end) become one sorted run; a run
 // without a partner is carried over.  A row of degree <= 2L is finished by
-// this round and goes straight to its final slots (col, edge, ladder);
+// this round and goes straight to its final slots (col, ladder);
 // longer rows go to out for the next round.  Block b writes positions
 // [qA + b kMergeTile, qA + (b + 1) kMergeTile) of [qA, T), qA the first
 // active row's start, piece by piece where the tile crosses a pair's end:
@@ -730,7 +732,7 @@ __global__ __launch_bounds__(THREADS) void k_hub_chunks(const int64_t *__restric
 __global__ __launch_bounds__(kBlock) void k_hub_merge(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
                                                       int64_t T, const uint32_t *__restrict__ hstart, int64_t H,
                                                       int64_t L, int64_t r0, int64_t p0, uint32_t *__restrict__ col,
-                                                      uint64_t *__restrict__ edge, uint32_t *__restrict__ ladder1)
+                                                      uint32_t *__restrict__ ladder1)
 {
     __shared__ uint32_t s_a[kMergeTile], s_b[kMergeTile], s_out[kMergeTile];
     __shared__ int64_t s_split[2];
@@ -797,7 +799,7 @@ __global__ __launch_bounds__(kBlock) void k_hub_merge(const uint32_t *__restrict
         __syncthreads();
         for (int o = t; o < n_out; o += kBlock) {
             if (last)
-                emit_slot(p0 + q + o, (uint32_t)(r0 + h), s_out[o], col, edge, ladder1);
+                emit_slot(p0 + q + o, s_out[o], col, ladder1);
             else
                 out[q + o] = s_out[o];
         }
@@ -832,55 +834,95 @@ __global__ __launch_bounds__(kBlock) void k_ladder_levels(const uint32_t *__rest
 // Launch 1 of the weights scan, written out for memory-level parallelism:
 // both weights of every slot and their inclusive prefix sums inside the
 // slot's segment of kPrefixSeg slots (one wave: kWItems rows of 64), and one
-// pair of sums per segment.  Each thread issues the loads of kWBatch items
-// before any store, so their gathers overlap; each row is one wave scan on
-// top of the running sum of the rows before it.
+// pair of sums per segment.  Each thread issues its column and reverse loads
+// before anything else, and the gathers of kWBatch items before their stores;
+// each row is one wave scan on top of the running sum of the rows before it.
+// What bounds it is memory: 44 bytes a slot in streams and the lines of the
+// gathers that miss (11.8 GB at 2.4e8 slots).  Batches of 4 keep four waves a
+// SIMD: 3.20 ms beside the row hash, 3.37 at 8 (three), 3.65 at 16.
 constexpr int kWItems = 16;
-constexpr int kWBatch = 16;
+constexpr int kWBatch = 4;
 static_assert((int64_t)kWave * kWItems == kPrefixSeg, "one wave per prefix segment");
 
-__global__ __launch_bounds__(kBlock) void k_weights_reduce(const uint64_t *__restrict__ edge,
+//
+// A slot's row comes from the segment's first row and the row starts inside
+// the segment, marked in a bitmap in LDS by the wave, instead of from an array
+// of rows: the row kernels write 8 bytes a slot less and this one reads 4 less
+// (R-MAT scale 22 from CSR to result: 11.03 -> 10.35 ms with the batches).
+__global__ __launch_bounds__(kBlock) void k_weights_reduce(const uint32_t *__restrict__ col,
+                                                           const uint32_t *__restrict__ seg_row,
                                                            const uint32_t *__restrict__ rev,
-                                                           const uint32_t *__restrict__ off, int64_t N,
-                                                           uint64_t *__restrict__ p_tau,
+                                                           const uint32_t *__restrict__ off, int64_t n,
+                                                           int64_t N, uint64_t *__restrict__ p_tau,
                                                            uint64_t *__restrict__ p_lam,
                                                            SlotRec *__restrict__ rec, U64x2 *__restrict__ seg_sums,
                                                            PrepStats *st)
 {
-    const int w = threadIdx.x / kWave;
+    __shared__ uint64_t s_head[kBlock / kWave][kWItems];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int lane = lane_id();
     const int64_t seg = (int64_t)blockIdx.x * (kBlock / kWave) + w;
     const int64_t wave_base = seg * kPrefixSeg;
     if (wave_base >= N) return;  // wave-uniform; no barrier below
     uint32_t err = 0;
+    uint32_t v[kWItems], r[kWItems];
+#pragma unroll
+    for (int i = 0; i < kWItems; ++i) {
+        const int64_t idx = wave_base + (int64_t)i * kWave + lane;
+        const bool ok = idx < N;
+        // read once here: keep them out of the cache the gathers use
+        v[i] = ok ? __builtin_nontemporal_load(col + idx) : 0u;
+        r[i] = ok ? __builtin_nontemporal_load(rev + idx) : 0u;
+    }
+    // rows starting inside the segment after its first slot (none is empty:
+    // rows ascend by degree), one bit per slot; the LDS operations of one wave
+    // are in order
+    const uint32_t row0 = seg_row[seg];
+    uint64_t *const head = s_head[w];
+    if (lane < kWItems) head[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    const int64_t seg_end = wave_base + kPrefixSeg < N ? wave_base + kPrefixSeg : N;
+    for (int64_t q = (int64_t)row0 + 1;; q += kWave) {
+        const int64_t at = q + lane < n ? (int64_t)off[q + lane] : N;
+        const bool in = at < seg_end;
+        if (in) {
+            const uint32_t p = (uint32_t)(at - wave_base);
+            atomicOr(reinterpret_cast<unsigned long long *>(head + p / kWave), 1ull << (p % kWave));
+        }
+        if (__ballot(in) != ~0ull) break;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint64_t heads = lane < kWItems ? head[lane] : 0ull;
+    // the row of this lane's slot of item i: `before` the row of the slot
+    // before the item's first, then the heads up to the lane's own
+    const auto row_of = [&](int i, uint32_t &before) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)heads, i);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(heads >> 32), i);
+        const uint32_t own = (uint32_t)((((uint64_t)hi << 32 | lo) >> lane) & 1u);
+        const uint32_t row = before + own + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        before += (uint32_t)(__popc(lo) + __popc(hi));
+        return row;
+    };
     U64x2 carry{0, 0};
+    uint32_t rows = row0;
 #pragma unroll
     for (int h = 0; h < kWItems; h += kWBatch) {
-        uint64_t e[kWBatch];
-        uint32_t r[kWBatch];
+        uint32_t ou[kWBatch], ou1[kWBatch], ov[kWBatch], ov1[kWBatch], before = rows;
 #pragma unroll
         for (int i = 0; i < kWBatch; ++i) {
-            const int64_t idx = wave_base + (int64_t)(h + i) * kWave + lane;
-            const bool ok = idx < N;
-            // read once here: keep them out of the cache the gathers use
-            e[i] = ok ? __builtin_nontemporal_load(edge + idx) : 0ull;
-            r[i] = ok ? __builtin_nontemporal_load(rev + idx) : 0u;
-        }
-        uint32_t ou[kWBatch], ou1[kWBatch], ov[kWBatch], ov1[kWBatch];
-#pragma unroll
-        for (int i = 0; i < kWBatch; ++i) {
-            const uint32_t u = (uint32_t)e[i], v = (uint32_t)(e[i] >> 32);
+            const uint32_t u = row_of(h + i, before);
             ou[i] = off[u];
             ou1[i] = off[u + 1];
-            ov[i] = off[v];
-            ov1[i] = off[v + 1];
+            ov[i] = off[v[h + i]];
+            ov1[i] = off[v[h + i] + 1];
         }
 #pragma unroll
         for (int i = 0; i < kWBatch; ++i) {
             const int64_t idx = wave_base + (int64_t)(h + i) * kWave + lane;
+            const uint32_t u = row_of(h + i, rows);
             uint64_t tau = 0, lam = 0;
             if (idx < N) {
-                const int64_t rr = r[i];
+                const int64_t rr = r[h + i];
                 // symmetry: slot rev[i] (the i-th slot ordered by column) lies
                 // in row v.  Over all slots that makes every in-degree equal
                 // its out-degree (rev is a bijection), so the slots of column
@@ -896,9 +938,8 @@ __global__ __launch_bounds__(kBlock) void k_weights_reduce(const uint64_t *__res
             const U64x2 incl = wave_inclusive(U64x2{tau, lam}, PairSumOp(), U64x2{0, 0});
             if (idx < N) {
                 // the slot's sampler record: column, its row bounds, row
-                const uint32_t u = (uint32_t)e[i], v = (uint32_t)(e[i] >> 32);
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                const u32x4 r4 = {v, ov[i], ov1[i] - ov[i], u};
+                const u32x4 r4 = {v[h + i], ov[i], ov1[i] - ov[i], u};
                 __builtin_nontemporal_store(r4, reinterpret_cast<u32x4 *>(rec) + idx);
                 // whole 512-byte rows per instruction, read again only by the
                 // guide pass and the samplers: stream them past the cache
@@ -1288,24 +1329,23 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         hipLaunchKernelGGL(k_rank_from_order, dim3(grid_stream(n)), dim3(kBlock), 0, s, order, g->rank, n);
         PM_HIP(hipGetLastError());
     }
+    uint32_t *seg_row = nullptr;
+    PM_TRY(tmp.get(&seg_row, (size_t)prefix_segments(slots) + 1));
+    const OffOut off_out{g->off, seg_row, (uint64_t)prefix_segments(slots)};
     if (n == 0) {
         PM_TRY(fill_async<uint32_t>(g->off, 0u, 1, s));
     } else if (n <= kOneBlockScan) {
-        hipLaunchKernelGGL(k_off_scan, dim3(1), dim3(1024), 0, s, DegIn{g->deg}, OffOut{g->off}, n);
+        hipLaunchKernelGGL(k_off_scan, dim3(1), dim3(1024), 0, s, DegIn{g->deg}, off_out, n);
         PM_HIP(hipGetLastError());
     } else {
         char *scr = nullptr;
         PM_TRY(tmp.get(&scr, ScanScratch<uint64_t>::bytes_for(n, 16)));
-        PM_TRY((scan_launch<uint64_t, 16>(DegIn{g->deg}, OffOut{g->off}, n, SumOp<uint64_t>(), 0ull, scr, s)));
+        PM_TRY((scan_launch<uint64_t, 16>(DegIn{g->deg}, off_out, n, SumOp<uint64_t>(), 0ull, scr, s)));
     }
     const int vbits = bits_for(n > 0 ? (uint64_t)(n - 1) : 0);
     // the column array is padded to whole 128-byte lines (ladder level 0)
     const int64_t ssp = (ss + 31) / 32 * 32 + 32;
     PM_TRY(dev_alloc((void **)&g->col, sizeof(uint32_t) * ssp, s));
-    // (row, column) of every slot for the weights pass; the samplers read
-    // the slot records it writes
-    uint64_t *edge = nullptr;
-    PM_TRY(tmp.get(&edge, (size_t)ss));
     PM_TRY(dev_alloc((void **)&g->rec, sizeof(SlotRec) * ss, s));
     g->bytes += (sizeof(uint32_t) + sizeof(SlotRec)) * ss;
 
@@ -1351,13 +1391,12 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         if (cls[8] > cls[7]) {
             ProfScope pc("build_rows.b16384", side[1]);
             hipLaunchKernelGGL((k_rows_block<1024, 16>), dim3((unsigned)(cls[8] - cls[7])), dim3(1024), 0, side[1],
-                               off_in, col_in, order, g->rank, g->off, n, cls[7], vbits, g->col, edge, ladder1, st);
+                               off_in, col_in, order, g->rank, g->off, n, cls[7], vbits, g->col, ladder1, st);
         }
         if (cls[9] > cls[8]) {
             ProfScope pc("build_rows.b32768", side[1]);
             hipLaunchKernelGGL((k_rows_block_reg<1024, 32>), dim3((unsigned)(cls[9] - cls[8])), dim3(1024), 0,
-                               side[1], off_in, col_in, order, g->rank, g->off, n, cls[8], vbits, g->col, edge,
-                               ladder1, st);
+                               side[1], off_in, col_in, order, g->rank, g->off, n, cls[8], vbits, g->col, ladder1, st);
         }
         if (T > 0) {
             // hub rows: chunks sorted in blocks, then merged within each row
@@ -1372,49 +1411,48 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
             uint32_t *src = run0, *dst = run1;
             for (int64_t L = kHubChunk; L < (int64_t)g->dmax; L *= 2) {
                 hipLaunchKernelGGL(k_hub_merge, dim3((unsigned)((T + kMergeTile - 1) / kMergeTile)), dim3(kBlock), 0,
-                                   side[0], src, dst, T, hstart, H, L, rt, cls[kRowClasses], g->col, edge,
-                                   ladder1);
+                                   side[0], src, dst, T, hstart, H, L, rt, cls[kRowClasses], g->col, ladder1);
                 std::swap(src, dst);
             }
         }
         if (cls[1] > cls[0]) {
             ProfScope pc("build_rows.lane", s);
             hipLaunchKernelGGL(k_rows_group<16>, dim3((unsigned)((cls[1] - cls[0] + 15) / 16)), dim3(kBlock), 0, s,
-                               off_in, col_in, order, g->rank, g->off, n, cls[0], cls[1], g->col, edge, ladder1,
+                               off_in, col_in, order, g->rank, g->off, n, cls[0], cls[1], g->col, ladder1,
                                st);
         }
         if (cls[2] > cls[1]) {
             ProfScope pc("build_rows.wave", s);
             hipLaunchKernelGGL(k_rows_group<64>, dim3((unsigned)((cls[2] - cls[1] + 3) / 4)), dim3(kBlock), 0, s,
-                               off_in, col_in, order, g->rank, g->off, n, cls[1], cls[2], g->col, edge, ladder1,
+                               off_in, col_in, order, g->rank, g->off, n, cls[1], cls[2], g->col, ladder1,
                                st);
         }
         if (cls[3] > cls[2]) {
             ProfScope pc("build_rows.w128", s);
             hipLaunchKernelGGL(k_rows_bitonic<2>, dim3((unsigned)((cls[3] - cls[2] + 3) / 4)), dim3(kBlock), 0, s,
-                               off_in, col_in, order, g->rank, g->off, n, cls[2], cls[3], g->col, edge, ladder1,
+                               off_in, col_in, order, g->rank, g->off, n, cls[2], cls[3], g->col, ladder1,
                                st);
         }
         if (cls[4] > cls[3]) {
             ProfScope pc("build_rows.w256", s);
             hipLaunchKernelGGL(k_rows_bitonic<4>, dim3((unsigned)((cls[4] - cls[3] + 3) / 4)), dim3(kBlock), 0, s,
-                               off_in, col_in, order, g->rank, g->off, n, cls[3], cls[4], g->col, edge, ladder1,
+                               off_in, col_in, order, g->rank, g->off, n, cls[3], cls[4], g->col, ladder1,
                                st);
         }
         if (cls[5] > cls[4]) {
             ProfScope pc("build_rows.b1024", s);
             hipLaunchKernelGGL((k_rows_block_reg<64, 16>), dim3((unsigned)(cls[5] - cls[4])), dim3(64), 0, s, off_in,
-                               col_in, order, g->rank, g->off, n, cls[4], vbits, g->col, edge, ladder1, st);
+                               col_in, order, g->rank, g->off, n, cls[4], vbits, g->col, ladder1, st);
         }
         if (cls[6] > cls[5]) {
             ProfScope pc("build_rows.b4096", s);
             hipLaunchKernelGGL((k_rows_block_reg<256, 16>), dim3((unsigned)(cls[6] - cls[5])), dim3(256), 0, s, off_in,
-                               col_in, order, g->rank, g->off, n, cls[5], vbits, g->col, edge, ladder1, st);
+                               col_in, order, g->rank, g->off, n, cls[5], vbits, g->col, ladder1, st);
         }
         if (cls[7] > cls[6]) {
             ProfScope pc("build_rows.b8192", s);
             hipLaunchKernelGGL((k_rows_block_reg<512, 16>), dim3((unsigned)(cls[7] - cls[6])), dim3(512), 0, s, off_in,
-                               col_in, order, g->rank, g->off, n, cls[6], vbits, g->col, edge, ladder1, st);
+                               col_in, order, g->rank, g->off, n, cls[6], vbits, g->col, ladder1, st);
         }
         const hipError_t launched = hipGetLastError();
         PM_HIP(fork.join());  // before anything can return: the temporaries are released on s
@@ -1500,8 +1538,8 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         const int64_t tiles = (slots + (int64_t)kBlock * kWItems - 1) / ((int64_t)kBlock * kWItems);
         {
             ProfScope pr("weights.reduce", s);
-            hipLaunchKernelGGL(k_weights_reduce, dim3((unsigned)tiles), dim3(kBlock), 0, s, edge, rev, g->off,
-                               slots, g->p_tau, g->p_lam, g->rec, sums, st);
+            hipLaunchKernelGGL(k_weights_reduce, dim3((unsigned)tiles), dim3(kBlock), 0, s, g->col, seg_row, rev,
+                               g->off, n, slots, g->p_tau, g->p_lam, g->rec, sums, st);
             PM_HIP(hipGetLastError());
         }
         const SegOut seg_out{g->seg_tau, g->seg_lam, nseg, &st->totals};
