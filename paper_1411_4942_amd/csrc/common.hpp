@@ -96,6 +96,10 @@ __device__ __forceinline__ uint64_t draw_bounded(uint64_t seed, uint32_t tag, ui
     }
 }
 
+// Two neighbouring words as one 8-byte load from 4-byte alignment, which the
+// memory path allows.
+typedef uint32_t U32Pair __attribute__((ext_vector_type(2), aligned(4), may_alias));
+
 // q = a / d, r = a % d for a < 2^63 and 0 < d < 2^31 with a / d < 2^32:
 // a double-precision quotient (relative error 2^-52, so the truncated value is
 // off by at most one) corrected with exact integer arithmetic.

@@ -838,17 +838,20 @@ __global__ __launch_bounds__(kBlock) void k_ladder_levels(const uint32_t *__rest
 // before anything else, and the gathers of kWBatch items before their stores;
 // each row is one wave scan on top of the running sum of the rows before it.
 // What bounds it is memory: 44 bytes a slot in streams and the lines of the
-// gathers that miss (11.8 GB at 2.4e8 slots).  Batches of 4 keep four waves a
-// SIMD: 3.20 ms beside the row hash, 3.37 at 8 (three), 3.65 at 16.
+// gathers that miss (11.8 GB at 2.4e8 slots), then the gathers' requests: a
+// row's two bounds are one 8-byte load (3.20 -> 3.05 ms beside the row hash).
+// Batches of 8 keep four waves a SIMD; batches of 4 took 3.15 ms, of 16 (two
+// waves) 3.65 with the narrow loads.
 constexpr int kWItems = 16;
-constexpr int kWBatch = 4;
+constexpr int kWBatch = 8;
 static_assert((int64_t)kWave * kWItems == kPrefixSeg, "one wave per prefix segment");
 
 //
 // A slot's row comes from the segment's first row and the row starts inside
 // the segment, marked in a bitmap in LDS by the wave, instead of from an array
 // of rows: the row kernels write 8 bytes a slot less and this one reads 4 less
-// (R-MAT scale 22 from CSR to result: 11.03 -> 10.35 ms with the batches).
+// (R-MAT scale 22 from CSR to result: 11.03 -> 10.18 ms with the batches and
+// the wide loads).
 __global__ __launch_bounds__(kBlock) void k_weights_reduce(const uint32_t *__restrict__ col,
                                                            const uint32_t *__restrict__ seg_row,
                                                            const uint32_t *__restrict__ rev,
@@ -911,10 +914,10 @@ __global__ __launch_bounds__(kBlock) void k_weights_reduce(const uint32_t *__res
 #pragma unroll
         for (int i = 0; i < kWBatch; ++i) {
             const uint32_t u = row_of(h + i, before);
-            ou[i] = off[u];
-            ou1[i] = off[u + 1];
-            ov[i] = off[v[h + i]];
-            ov1[i] = off[v[h + i] + 1];
+            const U32Pair a = *reinterpret_cast<const U32Pair *>(off + u);
+            const U32Pair b = *reinterpret_cast<const U32Pair *>(off + v[h + i]);
+            ou[i] = a.x, ou1[i] = a.y;
+            ov[i] = b.x, ov1[i] = b.y;
         }
 #pragma unroll
         for (int i = 0; i < kWBatch; ++i) {
