@@ -231,9 +231,9 @@ typedef struct {
  * N_3 = sum_v t_v (d_v - 2), N_5 = sum_e C(t_e, 2) from triangles per edge;
  * N_4 (4-cycles) and N_6 (4-cliques) by enumeration under the degree order;
  * then Eq. 1 solved for C.  Work grows like the wedge count (hours-free up
- * to ~1e8 edges of power-law graphs); device scratch of 8 n bytes per
- * counting block (256 blocks) besides 4 bytes per slot.  Synchronises the
- * stream.  Errors: PM_EINVAL, PM_EOVERFLOW (a count >= 2^64), PM_ENOMEM,
+ * to ~1e8 edges of power-law graphs); device scratch of 4 bytes per slot and
+ * 24 per vertex, at most 1 GiB of bit rows and 4 GiB of row cursors.
+ * Synchronises the stream.  Errors: PM_EINVAL, PM_EOVERFLOW (a count >= 2^64), PM_ENOMEM,
  * PM_EDEVICE. */
 pm_status pm_exact_counts(const pm_graph *g, pm_exact *out, void *stream);
 

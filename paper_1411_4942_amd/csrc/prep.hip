@@ -3,12 +3,12 @@
 // N_1 (Algorithm 2) and the guide tables of the edge draw.
 //
 // The relabelled rows are built already sorted, one size class of rows per
-// launch (lane, wave and block sorts; global radix sorts for the few hub
+// launch (lane, wave and block sorts; chunk sorts and merges for the few hub
 // rows).  One stable sort of the finished slots by column then lists, at
 // position q, the slot holding the reverse of slot q: that permutation is at
 // once the symmetry check and the reverse slot map the lambda weights need.
-// The weights are parked with per-tile sums, and a second pass turns them
-// into both prefix sums and fills the guide tables.
+// The weights become prefix sums inside segments, the segments' sums are
+// scanned, and a second pass fills the guide tables.
 #include "graph.hpp"
 #include "profile.hpp"
 #include "radix.hpp"

@@ -1,7 +1,8 @@
 // The single-graph sampling kernels: Algorithm 1 (sample) classified as in
 // Algorithm 2, and Algorithm 3 (sample-centered) classified as in Algorithm 4
 // (the per-sample body is in sampler.hpp).  One lane per sample, grid-stride
-// over sample ids; per-lane counters, one wave reduction and atomic per class.
+// over sample ids (or over the ids sorted by their draws); the blocks' class
+// counts are rows that one kernel sums.
 #include "drawsort.hpp"
 #include "graph.hpp"
 #include "profile.hpp"
