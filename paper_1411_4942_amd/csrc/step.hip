@@ -267,10 +267,14 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
     uint64_t samples = 0;
     for (const StepItem &it : items) samples += it.count;
     if (samples == 0 || off || !draw_order_enabled() || samples < draw_order_min()) return PM_OK;
+    const auto too_small = [&](uint64_t parts) {
+        return parts > 1 && samples / parts < std::min<uint64_t>(draw_order_min(), kStepPartMin);
+    };
+    // (the least there can be, before the work of cutting them)
+    if (too_small((items.size() + kStepChunks - 1) / kStepChunks)) return PM_OK;
     try {
         const std::vector<HostPart> parts = cut_parts(items, samples);
-        if (parts.size() > 1 && samples / parts.size() < std::min<uint64_t>(draw_order_min(), kStepPartMin))
-            return PM_OK;
+        if (too_small(parts.size())) return PM_OK;
         size_t bytes = 0;
         uint64_t largest = 0;
         for (const HostPart &p : parts) {
