@@ -22,6 +22,7 @@
 #include "graph.hpp"
 #include "profile.hpp"
 #include "radix.hpp"
+#include "rowstarts.hpp"
 #include "scan.hpp"
 
 namespace pm {
@@ -130,10 +131,9 @@ __global__ __launch_bounds__(kBlock) void k_keep(const uint32_t *__restrict__ lo
     }
 }
 
-// Row starts of the sorted keys of K entries: start[v] = entries with a key
-// below v, v in [0, n].  Entry i (and a virtual entry K) sets the starts of
-// the rows after entry i - 1's up to its own; a block fills its long gaps
-// together.  kEach entries per thread, their loads together.
+// Row starts of the sorted keys of K entries (rowstarts.hpp): entry i sets
+// those of its span; a block fills its long spans together.  kEach entries per
+// thread, their loads together.
 constexpr uint32_t kGapAlone = 16;
 constexpr int kEach = 4;
 
@@ -145,22 +145,18 @@ __global__ __launch_bounds__(kBlock) void k_row_starts(const uint32_t *__restric
     if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * (kBlock * kEach) + threadIdx.x;
-    uint32_t v0[kEach], v1[kEach];  // the entry's rows [v0, v1], none when v0 > v1
+    RowSpan r[kEach];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) r[j] = row_span(key, K, n, base + j * kBlock);
 #pragma unroll
     for (int j = 0; j < kEach; ++j) {
         const int64_t i = base + j * kBlock;
-        v1[j] = i < K ? key[i] : (uint32_t)n;
-        v0[j] = i > 0 ? key[i <= K ? i - 1 : K - 1] + 1 : 0u;
-    }
-#pragma unroll
-    for (int j = 0; j < kEach; ++j) {
-        const int64_t i = base + j * kBlock;
-        if (v0[j] > v1[j] || i > K) continue;
-        if (v1[j] - v0[j] < kGapAlone) {
-            for (uint32_t v = v0[j]; v <= v1[j]; ++v) start[v] = (uint32_t)i;
+        if (r[j].first > r[j].last) continue;
+        if (r[j].last - r[j].first < kGapAlone) {
+            for (uint32_t v = r[j].first; v <= r[j].last; ++v) start[v] = (uint32_t)i;
         } else {
             const uint32_t q = atomicAdd(&s_n, 1u);
-            s_gap[q][0] = v0[j];
+            s_gap[q][0] = r[j].first;
             s_gap[q][1] = (uint32_t)i;
         }
     }
