@@ -29,6 +29,7 @@ enum : uint32_t {
     ERR_OVF_TAU = 32u,
     ERR_OVF_LAM = 64u,
     ERR_GUIDE = 128u,  // guide write out of range: only from inconsistent weights
+    ERR_ROWS = ERR_RANGE | ERR_LOOP | ERR_ORDER,  // what the row kernels check
 };
 
 // Row size classes: class c holds the rows with bound[c] < degree <=
@@ -1197,8 +1198,8 @@ void graph_free(pm_graph *g, hipStream_t s)
 constexpr int64_t kBesideSlots = 1ll << 22;
 
 // The row hash (rowhash.hip): `parts` is kRowHashSmall, kRowHashWide or both.
-pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t slot_at[5], uint32_t *H,
-                        hipStream_t s, int parts);
+pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t slot_at[5], RowVerdict verdict,
+                        uint32_t *H, hipStream_t s, int parts);
 
 // Device bytes a prepared graph of n vertices and `slots` directed slots
 // holds (what graph_create adds up in pm_graph::bytes).
@@ -1463,7 +1464,8 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     }
     // (the row checks are read back with the others at the end: the columns are
     // vertex ids whatever the input held, the sort and the weights' reads stay
-    // in range with any of them, and the guide is not filled after an error)
+    // in range with any of them and take the same time, and after an error the
+    // row hash is not built nor the guide filled)
     if (g->ladder_top > 1) {
         LadderLevels L{};
         L.base = g->ladder;
@@ -1492,11 +1494,12 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     Fork hfork(s, hside, beside ? 1 : 0);
     PM_HIP(hfork.status);
     hipStream_t hs = beside ? hside[0] : s;
+    const RowVerdict verdict{&st->err, ERR_ROWS};
     // row classes 0, 5..8: degree above 0, 1024, 4096, 8192, 16384
     const int64_t hrows[5] = {cls[0], cls[5], cls[6], cls[7], cls[8]};
     const int64_t hslot_at[5] = {cls[kRowClasses + 1 + 0], cls[kRowClasses + 1 + 5], cls[kRowClasses + 1 + 6],
                                  cls[kRowClasses + 1 + 7], cls[kRowClasses + 1 + 8]};
-    PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hs, kRowHashSmall));
+    PM_TRY(build_rowhash(g, hrows, hslot_at, verdict, g->hash, hs, kRowHashSmall));
 
     uint32_t *ka, *kb, *vfree, *v2a;
     PM_TRY(tmp.get(&ka, ss));
@@ -1511,7 +1514,7 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
                       &rev, false));
     Fork hfork2(s, hside, beside ? 1 : 0);  // the side stream now also waits for the reverse sort
     PM_HIP(hfork2.status);
-    PM_TRY(build_rowhash(g, hrows, hslot_at, g->hash, hs, kRowHashWide));
+    PM_TRY(build_rowhash(g, hrows, hslot_at, verdict, g->hash, hs, kRowHashWide));
 
     // weights, their prefixes and the guide tables of the edge draws (nothing
     // below indexes memory through the weights until the checks are read back)
@@ -1572,7 +1575,7 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
     // the scan writes its totals with the last segment offsets (seg[nseg]);
     // both stay 0 for an empty graph
     const uint64_t R[2] = {hst.totals.a, hst.totals.b};
-    if (hst.err & (ERR_RANGE | ERR_LOOP | ERR_ORDER | ERR_ASYM)) {
+    if (hst.err & (ERR_ROWS | ERR_ASYM)) {
         set_error(err_text(hst.err));
         return PM_EGRAPH;
     }

@@ -56,10 +56,12 @@ __device__ __forceinline__ void lds_insert(uint32_t *t, uint32_t size, uint32_t 
 // Their entries form one span of at most kHashSpan, built in LDS.
 __global__ __launch_bounds__(kBlock) void k_rowhash_small(const uint32_t *__restrict__ off,
                                                           const uint32_t *__restrict__ col, int64_t r_begin,
-                                                          int64_t r_end, int64_t s_end, uint32_t *__restrict__ H)
+                                                          int64_t r_end, int64_t s_end, RowVerdict rows,
+                                                          uint32_t *__restrict__ H)
 {
     __shared__ uint32_t t[kHashSpan];  // its first two words carry the block's row range first
     __shared__ uint32_t roff[kHashChunk + 1];
+    if (rows.bad()) return;
     const int64_t s0 = (int64_t)blockIdx.x * kHashChunk;
     const int64_t s1 = s0 + kHashChunk < s_end ? s0 + kHashChunk : s_end;
     if (threadIdx.x < 2) {  // first row starting at or after s0 (resp. s1); rows < 2^31
@@ -162,10 +164,11 @@ struct SpillList {
 // position stored at wstart[wbase(a) + w].
 __global__ __launch_bounds__(1024) void k_rowhash_sort(const uint32_t *__restrict__ off,
                                                        const uint32_t *__restrict__ col, int64_t r_begin,
-                                                       int64_t r_sort, uint32_t *__restrict__ part,
-                                                       uint32_t *__restrict__ wstart)
+                                                       int64_t r_sort, RowVerdict rows,
+                                                       uint32_t *__restrict__ part, uint32_t *__restrict__ wstart)
 {
     __shared__ uint32_t cnt[kHashGroup];
+    if (rows.bad()) return;
     const int64_t a = r_sort + blockIdx.x;
     const uint32_t rb = off[a], d = off[a + 1] - rb, size = 2u * d, nwin = window_count(d);
     const uint64_t wb = window_base(off, r_begin, a);
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(1024) void k_rowhash_sort(const uint32_t *__restric
 // continues from (the next window's first, or the row's first after the last).
 __global__ __launch_bounds__(kBlock) void k_rowhash_window(const uint32_t *__restrict__ off,
                                                            const uint32_t *__restrict__ col, int64_t r_begin,
-                                                           int64_t r_end, int64_t r_sort,
+                                                           int64_t r_end, int64_t r_sort, RowVerdict rows,
                                                            const uint32_t *__restrict__ part,
                                                            const uint32_t *__restrict__ wstart, SpillList *spill,
                                                            uint32_t *__restrict__ H)
@@ -214,6 +217,7 @@ __global__ __launch_bounds__(kBlock) void k_rowhash_window(const uint32_t *__res
     // 32 KiB in all, so that five blocks share a CU: the table's first word
     // carries the block's row first
     __shared__ uint32_t t[kHashWin];
+    if (rows.bad()) return;
     const uint64_t b = blockIdx.x;
     if (threadIdx.x == 0) {  // last row whose window base is <= b (rows < 2^31)
         int64_t lo = r_begin, hi = r_end;
@@ -265,8 +269,10 @@ __global__ __launch_bounds__(kBlock) void k_rowhash_window(const uint32_t *__res
 // their home to their window's end is taken, so this keeps the
 // linear-probing invariant.
 __global__ __launch_bounds__(kBlock) void k_rowhash_spill(const uint32_t *__restrict__ off, int64_t r_begin,
-                                                          const SpillList *spill, uint32_t *__restrict__ H)
+                                                          RowVerdict rows, const SpillList *spill,
+                                                          uint32_t *__restrict__ H)
 {
+    if (rows.bad()) return;
     const uint32_t n = spill->count < kSpillCap ? spill->count : kSpillCap;
     for (uint32_t i = (uint32_t)(blockIdx.x * blockDim.x + threadIdx.x); i < n; i += gridDim.x * blockDim.x) {
         const int64_t a = r_begin + spill->row[i];
@@ -280,9 +286,10 @@ __global__ __launch_bounds__(kBlock) void k_rowhash_spill(const uint32_t *__rest
 // home.
 __global__ __launch_bounds__(kBlock) void k_rowhash_repair(const uint32_t *__restrict__ off,
                                                            const uint32_t *__restrict__ col, int64_t r_begin,
-                                                           const SpillList *spill, uint32_t *__restrict__ H)
+                                                           RowVerdict rows, const SpillList *spill,
+                                                           uint32_t *__restrict__ H)
 {
-    if (!spill->overflow) return;
+    if (rows.bad() || !spill->overflow) return;
     const int64_t a = r_begin + blockIdx.x;
     const uint32_t rb = off[a], d = off[a + 1] - rb, size = 2u * d;
     uint32_t *out = H + 2ull * rb;
@@ -307,9 +314,10 @@ __global__ __launch_bounds__(kBlock) void k_rowhash_repair(const uint32_t *__res
 // 4096, 8192, 16384}, slot_at[c] = that row's first slot (rows ascend by
 // degree; rows before rows[0] have no slots).  H has 2 slots + kHashPad
 // entries.  `parts` selects the rows built (kRowHashSmall, kRowHashWide);
-// the two parts write disjoint entries and may run on different streams.
-pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t slot_at[5], uint32_t *H,
-                        hipStream_t s, int parts)
+// the two parts write disjoint entries and may run on different streams.  After
+// a failed row check the table is left unwritten.
+pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t slot_at[5], RowVerdict verdict,
+                        uint32_t *H, hipStream_t s, int parts)
 {
     const int64_t n = g->n, slots = g->slots;
     static_assert(2 * 4096 == kHashWin, "rows of degree up to 4096 are one window");
@@ -320,7 +328,7 @@ pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t 
         ProfScope pc("rowhash.small", s);
         const int64_t blocks = (small_end + kHashChunk - 1) / kHashChunk;
         hipLaunchKernelGGL(k_rowhash_small, dim3((unsigned)blocks), dim3(kBlock), 0, s, g->off, g->col, rows[0],
-                           rows[1], small_end, H);
+                           rows[1], small_end, verdict, H);
         PM_HIP(hipGetLastError());
     }
     if ((parts & kRowHashWide) && n > rows[1]) {
@@ -337,12 +345,12 @@ pm_status build_rowhash(const pm_graph *g, const int64_t rows[5], const int64_t 
         PM_TRY(fill_async<uint32_t>(&spill->count, 0u, 2, s));
         if (n > r_sort)
             hipLaunchKernelGGL(k_rowhash_sort, dim3((unsigned)(n - r_sort)), dim3(1024), 0, s, g->off, g->col, r_begin,
-                               r_sort, part, wstart);
+                               r_sort, verdict, part, wstart);
         hipLaunchKernelGGL(k_rowhash_window, dim3((unsigned)nblocks), dim3(kBlock), 0, s, g->off, g->col, r_begin, n,
-                           r_sort, part, wstart, spill, H);
-        hipLaunchKernelGGL(k_rowhash_spill, dim3(64), dim3(kBlock), 0, s, g->off, r_begin, spill, H);
+                           r_sort, verdict, part, wstart, spill, H);
+        hipLaunchKernelGGL(k_rowhash_spill, dim3(64), dim3(kBlock), 0, s, g->off, r_begin, verdict, spill, H);
         hipLaunchKernelGGL(k_rowhash_repair, dim3((unsigned)(n - r_begin)), dim3(kBlock), 0, s, g->off, g->col,
-                           r_begin, spill, H);
+                           r_begin, verdict, spill, H);
         PM_HIP(hipGetLastError());
     }
     return PM_OK;

@@ -24,6 +24,17 @@ constexpr int kHashSmallBound = 1024;
 // padding after the last row), the longer rows
 constexpr int kRowHashSmall = 1, kRowHashWide = 2;
 
+// What the build's row checks found, for the kernels that follow them: repeated
+// columns share a home and would each probe past all the others (d^2 / 2 steps
+// for a row of d), so no hash is built of rows that fail a check.  The word is
+// read under a mask of errors that no kernel still running can set, so every
+// thread of a block sees the same answer.
+struct RowVerdict {
+    const uint32_t *err;
+    uint32_t mask;
+    __device__ __forceinline__ bool bad() const { return (*err & mask) != 0; }
+};
+
 // MurmurHash3's 32-bit finalizer (Appleby, public domain): spreads the bits
 // of a column id over the word.
 __host__ __device__ __forceinline__ uint32_t hash_mix32(uint32_t h)
