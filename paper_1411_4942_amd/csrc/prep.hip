@@ -1218,6 +1218,126 @@ uint64_t graph_bytes_for(int64_t n, int64_t slots)
     return b;
 }
 
+// The build from the finished rows on: ladder levels, row hash, reverse slots,
+// weights and guides, all enqueued on s, with the side streams joined.  cls as
+// in graph_create; rscr holds radix_scratch_bytes(slots).
+static pm_status build_on_rows(pm_graph *g, const int64_t *cls, int vbits, char *rscr, const uint32_t *seg_row,
+                               PrepStats *st, Temps &tmp, hipStream_t s)
+{
+    const int64_t n = g->n, slots = g->slots, ss = std::max<int64_t>(slots, 1);
+    // (the row checks are read back with the others at the end: the columns are
+    // vertex ids whatever the input held, the sort and the weights' reads stay
+    // in range with any of them and take the same time, and after an error the
+    // row hash is not built nor the guide filled)
+    if (g->ladder_top > 1) {
+        LadderLevels L{};
+        L.base = g->ladder;
+        L.top = g->ladder_top;
+        for (int l = 2; l <= L.top; ++l) {
+            L.at[l] = g->ladder_off[l];
+            L.count[l] = ladder_count(slots, l);
+        }
+        hipLaunchKernelGGL(k_ladder_levels, dim3(grid_for((int64_t)L.count[2], kBlock, 1024)), dim3(kBlock), 0, s,
+                           g->col, L);
+        PM_HIP(hipGetLastError());
+    }
+    // the row hash of the adjacency tests (rows of degree <= 1024 many per
+    // block, longer ones in windows; rows above 4096 have several windows)
+    static_assert(kHashSmallBound == 1024, "row hash classes follow the row classes");
+    PM_TRY(dev_alloc((void **)&g->hash, sizeof(uint32_t) * (2 * ss + kHashPad), s));
+    g->bytes += sizeof(uint32_t) * (2 * ss + kHashPad);
+    // built on a side stream (it reads only the finished rows) and joined back
+    // before returning: the rows of degree <= 1024 beside the reverse sort,
+    // the longer ones beside the weights pass, so that each of the two
+    // shares the GPU with a part of the build.  Small graphs build it in line:
+    // the forks cost more than kernels of a few microseconds gain.
+    const bool beside = slots >= kBesideSlots;
+    hipStream_t hside[2];
+    PM_HIP(side_streams(hside));
+    Fork hfork(s, hside, beside ? 1 : 0);
+    PM_HIP(hfork.status);
+    hipStream_t hs = beside ? hside[0] : s;
+    const RowVerdict verdict{&st->err, ERR_ROWS};
+    // row classes 0, 5..8: degree above 0, 1024, 4096, 8192, 16384
+    const int64_t hrows[5] = {cls[0], cls[5], cls[6], cls[7], cls[8]};
+    const int64_t hslot_at[5] = {cls[kRowClasses + 1 + 0], cls[kRowClasses + 1 + 5], cls[kRowClasses + 1 + 6],
+                                 cls[kRowClasses + 1 + 7], cls[kRowClasses + 1 + 8]};
+    PM_TRY(build_rowhash(g, hrows, hslot_at, verdict, g->hash, hs, kRowHashSmall));
+
+    uint32_t *ka, *kb, *vfree, *v2a;
+    PM_TRY(tmp.get(&ka, ss));
+    PM_TRY(tmp.get(&kb, ss));
+    PM_TRY(tmp.get(&vfree, ss));
+    PM_TRY(tmp.get(&v2a, ss));
+
+    // reverse slots and the symmetry check: the slots' columns sorted stably,
+    // with each slot's own position as payload (only the payload is kept)
+    uint32_t *keys_unused, *rev;
+    PM_TRY(radix_sort("reverse_sort", RadixKeys{g->col}, kb, vfree, ka, v2a, slots, vbits, rscr, s, &keys_unused,
+                      &rev, false));
+    Fork hfork2(s, hside, beside ? 1 : 0);  // the side stream now also waits for the reverse sort
+    PM_HIP(hfork2.status);
+    PM_TRY(build_rowhash(g, hrows, hslot_at, verdict, g->hash, hs, kRowHashWide));
+
+    // weights, their prefixes and the guide tables of the edge draws (nothing
+    // below indexes memory through the weights until the checks are read back)
+    const int64_t nseg = prefix_segments(slots);
+    PM_TRY(dev_alloc((void **)&g->p_tau, sizeof(uint64_t) * ss, s));
+    PM_TRY(dev_alloc((void **)&g->p_lam, sizeof(uint64_t) * ss, s));
+    PM_TRY(dev_alloc((void **)&g->seg_tau, sizeof(uint64_t) * (nseg + 1), s));
+    PM_TRY(dev_alloc((void **)&g->seg_lam, sizeof(uint64_t) * (nseg + 1), s));
+    g->bytes += 2 * sizeof(uint64_t) * ss + 2 * sizeof(uint64_t) * (nseg + 1);
+    const uint64_t gtarget = guide_target(slots);
+    const uint64_t long_cap = gtarget / 64 + 2;
+    PM_TRY(dev_alloc((void **)&g->guide_tau, sizeof(uint32_t) * (gtarget + 1), s));
+    PM_TRY(dev_alloc((void **)&g->guide_lam, sizeof(uint32_t) * (gtarget + 1), s));
+    g->bytes += 2 * sizeof(uint32_t) * (gtarget + 1);
+    uint32_t *long_tau = nullptr, *long_lam = nullptr;
+    PM_TRY(tmp.get(&long_tau, long_cap));
+    PM_TRY(tmp.get(&long_lam, long_cap));
+    if (slots == 0) {
+        PM_TRY(fill_async<uint64_t>(g->seg_tau, 0ull, 1, s));
+        PM_TRY(fill_async<uint64_t>(g->seg_lam, 0ull, 1, s));
+    } else {
+        U64x2 *sums = nullptr;
+        char *scr = nullptr;
+        PM_TRY(tmp.get(&sums, (size_t)nseg));
+        PM_TRY(tmp.get(&scr, ScanScratch<U64x2>::bytes_for(nseg, 16)));
+        ProfScope prof("weights_scan", s);
+        const int64_t tiles = (slots + (int64_t)kBlock * kWItems - 1) / ((int64_t)kBlock * kWItems);
+        {
+            ProfScope pr("weights.reduce", s);
+            hipLaunchKernelGGL(k_weights_reduce, dim3((unsigned)tiles), dim3(kBlock), 0, s, g->col, seg_row, rev,
+                               g->off, n, slots, g->p_tau, g->p_lam, g->rec, sums, st);
+            PM_HIP(hipGetLastError());
+        }
+        const SegOut seg_out{g->seg_tau, g->seg_lam, nseg, &st->totals};
+        if (nseg <= kOneBlockScan) {
+            hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, s, SegIn{sums}, seg_out, nseg, st, slots,
+                               g->guide_tau, g->guide_lam);
+        } else {
+            PM_TRY((scan_launch<U64x2, 16>(SegIn{sums}, seg_out, nseg, PairSumOp(), U64x2{0, 0}, scr, s)));
+            hipLaunchKernelGGL(k_guide_setup, dim3(1), dim3(1), 0, s, st, slots, g->guide_tau, g->guide_lam);
+        }
+        PM_HIP(hipGetLastError());
+        {
+            ProfScope pg("weights.guide", s);
+            hipLaunchKernelGGL(k_guide_fill, dim3((unsigned)tiles), dim3(kBlock), 0, s, g->p_tau, g->p_lam,
+                               g->seg_tau, g->seg_lam, slots, g->guide_tau, g->guide_lam, long_tau, long_lam,
+                               (uint32_t)long_cap, st);
+            PM_HIP(hipGetLastError());
+        }
+        const GuideLong lt{g->p_tau, g->seg_tau, g->guide_tau, long_tau};
+        const GuideLong ll{g->p_lam, g->seg_lam, g->guide_lam, long_lam};
+        hipLaunchKernelGGL(k_guide_long, dim3((unsigned)std::min<uint64_t>(long_cap, 2048), 2), dim3(kBlock), 0, s, lt,
+                           ll, (uint32_t)long_cap, st);
+        PM_HIP(hipGetLastError());
+    }
+    PM_HIP(hfork2.join());
+    PM_HIP(hfork.join());
+    return PM_OK;
+}
+
 pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm_graph **out)
 {
     (void)flags;  // every check always runs: later kernels rely on them
@@ -1462,120 +1582,21 @@ pm_status graph_create(const pm_csr_view *csr, uint32_t flags, hipStream_t s, pm
         PM_HIP(fork.join());  // before anything can return: the temporaries are released on s
         PM_HIP(launched);
     }
-    // (the row checks are read back with the others at the end: the columns are
-    // vertex ids whatever the input held, the sort and the weights' reads stay
-    // in range with any of them and take the same time, and after an error the
-    // row hash is not built nor the guide filled)
-    if (g->ladder_top > 1) {
-        LadderLevels L{};
-        L.base = g->ladder;
-        L.top = g->ladder_top;
-        for (int l = 2; l <= L.top; ++l) {
-            L.at[l] = g->ladder_off[l];
-            L.count[l] = ladder_count(slots, l);
-        }
-        hipLaunchKernelGGL(k_ladder_levels, dim3(grid_for((int64_t)L.count[2], kBlock, 1024)), dim3(kBlock), 0, s,
-                           g->col, L);
-        PM_HIP(hipGetLastError());
+    // Whatever came of the rest, the row kernels are waited for before anything
+    // returns (they read the caller's arrays), and a graph that fails a row
+    // check is refused for that, also where memory ran out on the way.
+    const pm_status built = build_on_rows(g, cls, vbits, rscr, seg_row, st, tmp, s);
+    const hipError_t read = slot.read_back(&hst, st, sizeof(hst), s);
+    if (read == hipSuccess && (hst.err & ERR_ROWS)) {
+        set_error(err_text(hst.err));
+        return PM_EGRAPH;
     }
-    // the row hash of the adjacency tests (rows of degree <= 1024 many per
-    // block, longer ones in windows; rows above 4096 have several windows)
-    static_assert(kHashSmallBound == 1024, "row hash classes follow the row classes");
-    PM_TRY(dev_alloc((void **)&g->hash, sizeof(uint32_t) * (2 * ss + kHashPad), s));
-    g->bytes += sizeof(uint32_t) * (2 * ss + kHashPad);
-    // built on a side stream (it reads only the finished rows) and joined back
-    // before returning: the rows of degree <= 1024 beside the reverse sort,
-    // the longer ones beside the weights pass, so that each of the two
-    // shares the GPU with a part of the build.  Small graphs build it in line:
-    // the forks cost more than kernels of a few microseconds gain.
-    const bool beside = slots >= kBesideSlots;
-    hipStream_t hside[2];
-    PM_HIP(side_streams(hside));
-    Fork hfork(s, hside, beside ? 1 : 0);
-    PM_HIP(hfork.status);
-    hipStream_t hs = beside ? hside[0] : s;
-    const RowVerdict verdict{&st->err, ERR_ROWS};
-    // row classes 0, 5..8: degree above 0, 1024, 4096, 8192, 16384
-    const int64_t hrows[5] = {cls[0], cls[5], cls[6], cls[7], cls[8]};
-    const int64_t hslot_at[5] = {cls[kRowClasses + 1 + 0], cls[kRowClasses + 1 + 5], cls[kRowClasses + 1 + 6],
-                                 cls[kRowClasses + 1 + 7], cls[kRowClasses + 1 + 8]};
-    PM_TRY(build_rowhash(g, hrows, hslot_at, verdict, g->hash, hs, kRowHashSmall));
-
-    uint32_t *ka, *kb, *vfree, *v2a;
-    PM_TRY(tmp.get(&ka, ss));
-    PM_TRY(tmp.get(&kb, ss));
-    PM_TRY(tmp.get(&vfree, ss));
-    PM_TRY(tmp.get(&v2a, ss));
-
-    // reverse slots and the symmetry check: the slots' columns sorted stably,
-    // with each slot's own position as payload (only the payload is kept)
-    uint32_t *keys_unused, *rev;
-    PM_TRY(radix_sort("reverse_sort", RadixKeys{g->col}, kb, vfree, ka, v2a, slots, vbits, rscr, s, &keys_unused,
-                      &rev, false));
-    Fork hfork2(s, hside, beside ? 1 : 0);  // the side stream now also waits for the reverse sort
-    PM_HIP(hfork2.status);
-    PM_TRY(build_rowhash(g, hrows, hslot_at, verdict, g->hash, hs, kRowHashWide));
-
-    // weights, their prefixes and the guide tables of the edge draws (nothing
-    // below indexes memory through the weights until the checks are read back)
-    const int64_t nseg = prefix_segments(slots);
-    PM_TRY(dev_alloc((void **)&g->p_tau, sizeof(uint64_t) * ss, s));
-    PM_TRY(dev_alloc((void **)&g->p_lam, sizeof(uint64_t) * ss, s));
-    PM_TRY(dev_alloc((void **)&g->seg_tau, sizeof(uint64_t) * (nseg + 1), s));
-    PM_TRY(dev_alloc((void **)&g->seg_lam, sizeof(uint64_t) * (nseg + 1), s));
-    g->bytes += 2 * sizeof(uint64_t) * ss + 2 * sizeof(uint64_t) * (nseg + 1);
-    const uint64_t gtarget = guide_target(slots);
-    const uint64_t long_cap = gtarget / 64 + 2;
-    PM_TRY(dev_alloc((void **)&g->guide_tau, sizeof(uint32_t) * (gtarget + 1), s));
-    PM_TRY(dev_alloc((void **)&g->guide_lam, sizeof(uint32_t) * (gtarget + 1), s));
-    g->bytes += 2 * sizeof(uint32_t) * (gtarget + 1);
-    uint32_t *long_tau = nullptr, *long_lam = nullptr;
-    PM_TRY(tmp.get(&long_tau, long_cap));
-    PM_TRY(tmp.get(&long_lam, long_cap));
-    if (slots == 0) {
-        PM_TRY(fill_async<uint64_t>(g->seg_tau, 0ull, 1, s));
-        PM_TRY(fill_async<uint64_t>(g->seg_lam, 0ull, 1, s));
-    } else {
-        U64x2 *sums = nullptr;
-        char *scr = nullptr;
-        PM_TRY(tmp.get(&sums, (size_t)nseg));
-        PM_TRY(tmp.get(&scr, ScanScratch<U64x2>::bytes_for(nseg, 16)));
-        ProfScope prof("weights_scan", s);
-        const int64_t tiles = (slots + (int64_t)kBlock * kWItems - 1) / ((int64_t)kBlock * kWItems);
-        {
-            ProfScope pr("weights.reduce", s);
-            hipLaunchKernelGGL(k_weights_reduce, dim3((unsigned)tiles), dim3(kBlock), 0, s, g->col, seg_row, rev,
-                               g->off, n, slots, g->p_tau, g->p_lam, g->rec, sums, st);
-            PM_HIP(hipGetLastError());
-        }
-        const SegOut seg_out{g->seg_tau, g->seg_lam, nseg, &st->totals};
-        if (nseg <= kOneBlockScan) {
-            hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, s, SegIn{sums}, seg_out, nseg, st, slots,
-                               g->guide_tau, g->guide_lam);
-        } else {
-            PM_TRY((scan_launch<U64x2, 16>(SegIn{sums}, seg_out, nseg, PairSumOp(), U64x2{0, 0}, scr, s)));
-            hipLaunchKernelGGL(k_guide_setup, dim3(1), dim3(1), 0, s, st, slots, g->guide_tau, g->guide_lam);
-        }
-        PM_HIP(hipGetLastError());
-        {
-            ProfScope pg("weights.guide", s);
-            hipLaunchKernelGGL(k_guide_fill, dim3((unsigned)tiles), dim3(kBlock), 0, s, g->p_tau, g->p_lam,
-                               g->seg_tau, g->seg_lam, slots, g->guide_tau, g->guide_lam, long_tau, long_lam,
-                               (uint32_t)long_cap, st);
-            PM_HIP(hipGetLastError());
-        }
-        const GuideLong lt{g->p_tau, g->seg_tau, g->guide_tau, long_tau}, ll{g->p_lam, g->seg_lam, g->guide_lam, long_lam};
-        hipLaunchKernelGGL(k_guide_long, dim3((unsigned)std::min<uint64_t>(long_cap, 2048), 2), dim3(kBlock), 0, s, lt,
-                           ll, (uint32_t)long_cap, st);
-        PM_HIP(hipGetLastError());
-    }
-    PM_HIP(hfork2.join());
-    PM_HIP(hfork.join());
-    PM_HIP(slot.read_back(&hst, st, sizeof(hst), s));
+    PM_TRY(built);
+    PM_HIP(read);
     // the scan writes its totals with the last segment offsets (seg[nseg]);
     // both stay 0 for an empty graph
     const uint64_t R[2] = {hst.totals.a, hst.totals.b};
-    if (hst.err & (ERR_ROWS | ERR_ASYM)) {
+    if (hst.err & ERR_ASYM) {
         set_error(err_text(hst.err));
         return PM_EGRAPH;
     }
