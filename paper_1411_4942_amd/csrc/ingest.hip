@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_row_starts(const uint32_t *__restric
 #pragma unroll
     for (int j = 0; j < kEach; ++j) {
         const int64_t i = base + j * kBlock;
-        if (r[j].first > r[j].last) continue;
+        if (r[j].first > r[j].last || i > K) continue;
         if (r[j].last - r[j].first < kGapAlone) {
             for (uint32_t v = r[j].first; v <= r[j].last; ++v) start[v] = (uint32_t)i;
         } else {
