@@ -234,8 +234,12 @@ pm_status csr_from_edges_impl(const pm_edge_view *ev, int64_t *off, int32_t *col
     IngestState *st = nullptr, hst{};
     char *scr = nullptr;
     uint32_t *k0, *v0, *k1, *v1, *sums = nullptr;
+    const int64_t tiles = (E + kKeepTile - 1) / kKeepTile;
+    // (all of it before the first kernel that reads the pairs: up to the read
+    // back nothing returns for want of memory while the caller's arrays are read)
     PM_TRY(tmp.get(&st, 1));
     PM_TRY(fill_async<uint32_t>((uint32_t *)st, 0u, 2, s));
+    PM_TRY(tmp.get(&sums, (size_t)tiles));
     PM_TRY(tmp.get(&scr, radix_scratch_bytes(E)));
     PM_TRY(tmp.get(&k0, ee));
     PM_TRY(tmp.get(&v0, ee));
@@ -249,8 +253,6 @@ pm_status csr_from_edges_impl(const pm_edge_view *ev, int64_t *off, int32_t *col
     PM_TRY(radix_sort("ingest.sort_low", RadixPairs{lo, hi}, kf, vf, hi, lo, E, bits, scr, s, &lo_s, &hi_s));
     // the kept pairs into the other buffers
     uint32_t *lo_u = lo_s == kf ? hi : kf, *hi_u = hi_s == vf ? lo : vf;
-    const int64_t tiles = (E + kKeepTile - 1) / kKeepTile;
-    PM_TRY(tmp.get(&sums, (size_t)tiles));
     {
         ProfScope prof("ingest.dedup", s);
         hipLaunchKernelGGL(k_keep<false>, dim3((unsigned)tiles), dim3(kBlock), 0, s, lo_s, hi_s, E, sums, nullptr,
