@@ -435,12 +435,14 @@ pm_status launch_alias(const pm_graph *g, bool centered, uint64_t seed, uint64_t
     ProfScope prof(centered ? "sample_centered_alias" : "sample_path_alias", s);
     if (k >= draw_order_min() && N > 1 && draw_order_enabled())
         return launch_alias_sorted(v, T, N, centered, seed, first, k, tally, (unsigned)cap, s);
-    if (centered)
-        hipLaunchKernelGGL((k_sample_alias<true>), dim3(blocks), dim3(kBlock), 0, s, v, T, N, seed, first, k,
-                           (unsigned long long *)tally);
-    else
-        hipLaunchKernelGGL((k_sample_alias<false>), dim3(blocks), dim3(kBlock), 0, s, v, T, N, seed, first, k,
-                           (unsigned long long *)tally);
+    for_launches(k, blocks, [&](uint64_t at, uint64_t kc) {
+        if (centered)
+            hipLaunchKernelGGL((k_sample_alias<true>), dim3(blocks), dim3(kBlock), 0, s, v, T, N, seed, first + at, kc,
+                               (unsigned long long *)tally);
+        else
+            hipLaunchKernelGGL((k_sample_alias<false>), dim3(blocks), dim3(kBlock), 0, s, v, T, N, seed, first + at,
+                               kc, (unsigned long long *)tally);
+    });
     PM_HIP(hipGetLastError());
     return PM_OK;
 }

@@ -332,9 +332,9 @@ static pm_status launch_sorted(const SampleShape &sh, const SamplerView &v, bool
 }
 
 // One sampler's k samples from id `first`: into tally (device, added to), or
-// with `parts` (an id-order launch, sh.cap <= kMaxTallyParts), as *rows rows
-// of parts.  Draw-ordered launches take their buffers from `fixed` when
-// given, else from the allocator.
+// with `parts` (one id-order launch: sh.cap <= kMaxTallyParts, k <=
+// max_launch_samples(sh.cap)), as *rows rows of parts.  Draw-ordered launches
+// take their buffers from `fixed` when given, else from the allocator.
 static pm_status launch_sampler(const SampleShape &sh, const pm_graph *g, bool centered, uint64_t seed,
                                 uint64_t first, uint64_t k, uint64_t *tally, hipStream_t s,
                                 const DrawSortBufs *fixed = nullptr, uint64_t *parts = nullptr,
@@ -351,9 +351,9 @@ static pm_status launch_sampler(const SampleShape &sh, const pm_graph *g, bool c
         return fixed ? launch_sorted_in(sh, v, centered, seed, first, k, tally, s, *fixed)
                      : launch_sorted(sh, v, centered, seed, first, k, tally, s);
     unsigned long long *t = (unsigned long long *)tally, *q = (unsigned long long *)parts;
-    if (parts) *rows = blocks;  // k <= kMaxLaunchSamples then: one launch
-    for (uint64_t at = 0; at < k; at += kMaxLaunchSamples) {
-        const uint64_t id = first + at, kc = std::min(k - at, kMaxLaunchSamples);
+    if (parts) *rows = blocks;  // one launch then
+    for_launches(k, blocks, [&](uint64_t at, uint64_t kc) {
+        const uint64_t id = first + at;
         if (wave) {
             if (centered)
                 hipLaunchKernelGGL((k_sample_wave<true, false>), dim3(blocks), dim3(kBlock), 0, s, v, seed, id, kc,
@@ -371,8 +371,8 @@ static pm_status launch_sampler(const SampleShape &sh, const pm_graph *g, bool c
             default: launch_k_sample<true, 4>(sh.mode, blocks, s, v, seed, id, kc, t, q); break;
             }
         }
-        PM_HIP(hipGetLastError());
-    }
+    });
+    PM_HIP(hipGetLastError());
     return PM_OK;
 }
 
@@ -545,7 +545,7 @@ static pm_status sample_into(const pm_graph *g, const pm_params *p, uint64_t *ta
     PM_TRY(check_device(g));
     const SampleShape sh(g);
     const bool pair = sh.one_chunk(g->R_tau, p->k_path) && sh.one_chunk(g->R_lam, p->k_cent);
-    if (std::max(sh.cap, sh.order_cap) > kMaxTallyParts || std::max(p->k_path, p->k_cent) > kMaxLaunchSamples ||
+    if (std::max(sh.cap, sh.order_cap) > kMaxTallyParts || std::max(p->k_path, p->k_cent) > max_launch_samples(sh.cap) ||
         (!pair && (sh.sorted(g->R_tau, p->k_path) || sh.sorted(g->R_lam, p->k_cent))))
         scratch = nullptr;
     if (!scratch) PM_TRY(fill_async<uint64_t>(tallies_dev, 0ull, 2 * PM_NUM_TALLIES, s));

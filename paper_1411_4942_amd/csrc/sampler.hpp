@@ -10,6 +10,7 @@
 
 #include "graph.hpp"
 #include "ladder_wave.hpp"
+#include "launchsplit.hpp"
 #include "rowhash.hpp"
 
 namespace pm {
@@ -240,7 +241,7 @@ uint64_t draw_order_min();
 struct WaveTally {
     uint32_t c[PM_NUM_TALLIES] = {0};
 };
-constexpr uint64_t kMaxLaunchSamples = 1ull << 40;  // a wave counts below 2^32 (256 or more blocks share them)
+static_assert(kBlockWaves == kBlock / kWave, "the launches are split by the kernels' waves");
 
 __device__ __forceinline__ void tally_count(WaveTally &t, uint32_t cls)
 {
