@@ -329,7 +329,7 @@ pm_status grow_tiles(pm_server *S, uint32_t need)
 
 // Cut this step's chunks: the pilot whole, otherwise an equal share of
 // step_samples per (request, sampler) with work left, in whole tiles.
-// *samples receives their sum.
+// *samples receives their sum (at most 2^64 - 1: pilots may be of any size).
 void cut_chunks(pm_server *S, uint64_t *samples)
 {
     const uint64_t tile = (uint64_t)S->cfg.samples_per_tile;
@@ -344,7 +344,7 @@ void cut_chunks(pm_server *S, uint64_t *samples)
         for (int tag = 0; tag < 2; ++tag) {
             const uint64_t rem = target_of(S, r, tag) - std::min(r->next[tag], target_of(S, r, tag));
             r->chunk[tag] = r->sized ? std::min(rem, share) : rem;
-            *samples += r->chunk[tag];
+            if (__builtin_add_overflow(*samples, r->chunk[tag], samples)) *samples = ~0ull;
         }
 }
 

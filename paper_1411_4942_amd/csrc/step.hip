@@ -258,6 +258,10 @@ void StepRunner::free(hipStream_t s)
 // step into parts of kStepChunks chunks; below this size a part's launches
 // (about 60 us) cost what the order saves.
 constexpr uint64_t kStepPartMin = 1ull << 20;
+// Above this (2^16 parts, minutes of sampling) a step is left to the id order
+// too, which refuses what its tile table cannot hold: the parts' tables would
+// grow with a budget of any size.
+constexpr uint64_t kStepMax = kSortedChunk << 16;
 
 pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items, uint64_t *tallies, int64_t slots,
                           unsigned blocks, hipStream_t s, bool *done)
@@ -265,7 +269,10 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
     *done = false;
     bool enqueued = false;
     uint64_t samples = 0;
-    for (const StepItem &it : items) samples += it.count;
+    for (const StepItem &it : items) {
+        if (it.count > kStepMax - samples) return PM_OK;
+        samples += it.count;
+    }
     if (samples == 0 || off || !draw_order_enabled() || samples < draw_order_min()) return PM_OK;
     const auto too_small = [&](uint64_t parts) {
         return parts > 1 && samples / parts < std::min<uint64_t>(draw_order_min(), kStepPartMin);

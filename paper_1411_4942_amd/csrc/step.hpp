@@ -54,8 +54,8 @@ public:
     // Enqueue the items' samples: tallies[0, slots * 16) receive their counts
     // (slot * 16 + tag * 8 + c; zero elsewhere).  No two items share a slot
     // and a sampler.  *done is false, and nothing is enqueued, where the step
-    // is left to the id order: fewer than draw_order_min() samples, draw
-    // order off, too many small items, or no memory.
+    // is left to the id order: fewer than draw_order_min() samples or more
+    // than 2^40, draw order off, too many small items, or no memory.
     pm_status run(const BatchGraph *graphs, std::vector<StepItem> &items, uint64_t *tallies, int64_t slots,
                   unsigned blocks, hipStream_t s, bool *done);
     void free(hipStream_t s);
