@@ -114,6 +114,7 @@ struct pm_server {
     unsigned max_blocks = 1;    // of an id-order step
     unsigned order_blocks = 1;  // of a draw-ordered one
     pm::StepRunner order;  // draw-ordered steps
+    std::vector<pm::StepItem> items;  // the step's, with room for those of max_active requests
 };
 
 namespace pm {
@@ -387,16 +388,15 @@ pm_status launch_step(pm_server *S, bool *launched)
     const size_t tb = sizeof(uint64_t) * (size_t)S->cfg.max_active * 2 * PM_NUM_TALLIES;
     PM_HIP(hipEventRecord(S->ev_a, S->s_step));
     bool ordered = false;
-    std::vector<StepItem> items;
-    items.reserve(2 * S->active.size());
+    S->items.clear();
     for (SrvReq *r : S->active) {
         const pm_graph *g = S->graphs[r->rq.graph].g;
         for (int tag = 0; tag < 2; ++tag)
             if (r->chunk[tag])
-                items.push_back({r->rq.graph, (uint32_t)tag, (uint32_t)r->slot, r->next[tag], r->chunk[tag], r->rq.seed,
-                                 tag == 0 ? g->R_tau : g->R_lam});
+                S->items.push_back({r->rq.graph, (uint32_t)tag, (uint32_t)r->slot, r->next[tag], r->chunk[tag],
+                                    r->rq.seed, tag == 0 ? g->R_tau : g->R_lam});
     }
-    PM_TRY(S->order.run(S->d_graphs, items, S->d_tallies, S->cfg.max_active, S->order_blocks, S->s_step,
+    PM_TRY(S->order.run(S->d_graphs, S->items, S->d_tallies, S->cfg.max_active, S->order_blocks, S->s_step,
                         &ordered));
     if (!ordered) {
         uint32_t ntiles = 0;
@@ -590,6 +590,7 @@ pm_status server_create(const pm_server_cfg *cfg_in, pm_server **out)
     }
     S->cfg = c;
     S->graphs.reserve((size_t)c.max_graphs);
+    S->items.reserve(2 * (size_t)c.max_active);
     for (int i = c.max_active - 1; i >= 0; --i) S->free_slots.push_back(i);
     PM_HIP(hipStreamCreateWithFlags(&S->s_step, hipStreamNonBlocking));
     PM_HIP(hipStreamCreateWithFlags(&S->s_prep, hipStreamNonBlocking));
