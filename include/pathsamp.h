@@ -290,9 +290,9 @@ typedef struct pm_batch pm_batch;
  * reset, kernel, tally download) is captured once as a HIP graph on an
  * internal stream and replayed by pm_batch_run.  Runs of pm_set_draw_order's
  * samples or more are launched in draw order instead, the samples of all the
- * graphs sorted together (with at most 0.3 GB of buffers, kept until
- * pm_batch_destroy; without memory for them the graph is replayed).  The
- * batch keeps pointers to the graphs: destroy the batch before them.
+ * graphs sorted together (with at most 0.3 GB of buffers for the run, from the
+ * library's cached memory; without memory for them the graph is replayed).
+ * The batch keeps pointers to the graphs: destroy the batch before them.
  * Errors: PM_EINVAL (null, count <= 0, a graph on another device, k_path = k_cent = 0, delta outside
  * (0,1), bad tune), PM_ENOMEM, PM_EDEVICE. */
 pm_status pm_batch_create(const pm_graph *const *graphs, const pm_params *params, int32_t count, const pm_tune *tune,
@@ -323,8 +323,8 @@ pm_status pm_count_batch(const pm_graph *const *graphs, const pm_params *params,
  * request needs them (and keeps them resident within an HBM budget), and
  * runs requests in steps: each step samples a chunk of every active request,
  * in draw order from the samples of pm_set_draw_order on (with at most 0.3 GB
- * of buffers beside the HBM budget, kept until pm_server_destroy; without
- * memory for them in id order), else as one persistent launch over work
+ * of buffers for the step, from the library's cached memory, beside the HBM
+ * budget; without memory for them in id order), else as one persistent launch over work
  * tiles.  Requests that arrive while others run are admitted between steps
  * and share the device with them.  A request either
  * gives its sample budgets or asks for a relative error: then its first

@@ -213,44 +213,40 @@ pm_status launch_part(const BatchGraph *graphs, const HostPart &p, const char *t
 
 }  // namespace
 
-// The buffers; false (and id-order steps from then on) when the device or the
-// host has no memory for them.
-bool StepRunner::grow(size_t bytes, uint64_t part, hipStream_t s)
+// Room for the parts' tables; false when the device or the host has no memory.
+bool StepRunner::grow(size_t bytes, hipStream_t s)
 {
-    bool ok = true;
-    if (bytes > table_cap) {
-        dev_free(d_tables, s);
-        if (h_tables) (void)hipHostFree(h_tables);
-        d_tables = h_tables = nullptr;
-        table_cap = 0;
-        ok = dev_alloc((void **)&d_tables, 2 * bytes, s) == PM_OK &&
-             hipHostMalloc((void **)&h_tables, 2 * bytes, hipHostMallocDefault) == hipSuccess;
-        if (ok) table_cap = 2 * bytes;
-    }
-    if (ok && part > order_cap) {
-        dev_free(d_order, s);
-        d_order = nullptr;
-        order_cap = 0;
-        const uint64_t cap = std::min<uint64_t>(kSortedChunk, std::max<uint64_t>(part + part / 4, 1u << 20));
-        ok = dev_alloc((void **)&d_order, draw_sort_bytes(cap) + 4 * kCountWords, s) == PM_OK;
-        if (ok) order_cap = cap;
-    }
-    if (!ok) {
+    if (bytes <= table_cap) return true;
+    dev_free(d_tables, s);
+    if (h_tables) (void)hipHostFree(h_tables);
+    d_tables = h_tables = nullptr;
+    table_cap = 0;
+    if (dev_alloc((void **)&d_tables, 2 * bytes, s) != PM_OK) return false;
+    if (hipHostMalloc((void **)&h_tables, 2 * bytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
-        off = true;
+        return false;
     }
-    return ok;
+    table_cap = 2 * bytes;
+    return true;
 }
 
 void StepRunner::free(hipStream_t s)
 {
     dev_free(d_tables, s);
-    dev_free(d_order, s);
     if (h_tables) (void)hipHostFree(h_tables);
-    d_tables = h_tables = d_order = nullptr;
+    d_tables = h_tables = nullptr;
     table_cap = 0;
-    order_cap = 0;
 }
+
+// Positions that the sort's buffers of a part are taken for: a power of two, so
+// that steps of any size reuse few blocks of the library's cache.
+static uint64_t order_positions(uint64_t part)
+{
+    uint64_t cap = 1ull << 20;
+    while (cap < part) cap <<= 1;
+    return cap;
+}
+static_assert((kSortedChunk & (kSortedChunk - 1)) == 0, "the largest part is a power of two");
 
 // A step of one part pays from draw_order_min() samples on (64 graphs of up to
 // 2e6 edges at 2.6e6 samples in all: 0.77 ms in id order, 0.44 ms ordered; one
@@ -291,7 +287,15 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
         bytes += table_bytes(p);
         largest = std::max<uint64_t>(largest, p.samples);
     }
-    if (!grow(bytes, largest, s)) return PM_OK;
+    // the sort's buffers, then the blocks' counts: the library's cached memory
+    // for the step, as pm_count's
+    Temps tmp(s);
+    const uint64_t cap = order_positions(largest);
+    char *order = nullptr;
+    if (!grow(bytes, s) || tmp.get(&order, draw_sort_bytes(cap) + 4 * kCountWords) != PM_OK) {
+        off = true;
+        return PM_OK;
+    }
     size_t at = 0;
     for (const HostPart &p : parts) {  // (both tables are multiples of 8 bytes)
         const size_t c = p.chunks.size() * sizeof(StepChunk);
@@ -300,8 +304,8 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
         at += table_bytes(p);
     }
     DrawSortBufs b{};
-    draw_sort_carve(d_order, order_cap, &b);
-    uint32_t *counts = reinterpret_cast<uint32_t *>(d_order + draw_sort_bytes(order_cap));
+    draw_sort_carve(order, cap, &b);
+    uint32_t *counts = reinterpret_cast<uint32_t *>(order + draw_sort_bytes(cap));
     const auto enqueue = [&]() -> pm_status {
         PM_HIP(hipMemcpyAsync(d_tables, h_tables, bytes, hipMemcpyHostToDevice, s));
         PM_TRY(fill_async<uint64_t>(tallies, 0ull, slots * 2 * PM_NUM_TALLIES, s));

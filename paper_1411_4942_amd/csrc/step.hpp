@@ -46,9 +46,11 @@ constexpr unsigned kStepBlocks = 2048;  // blocks of a launch, at most (more wou
 // slower: 13.8 ms at 4, 16.3 at 8, over the requests of step.hip).
 constexpr int kStepBlocksPerCu = 6;
 
-// Runs draw-ordered steps on one stream, with buffers grown to the largest
-// step seen (at most those of a part of kSortedChunk samples).  One step at a
-// time: the caller has waited for the step before.
+// Runs draw-ordered steps on one stream.  It keeps the tables' memory; a step's
+// sort buffers (at most those of a part of kSortedChunk samples, 0.3 GB) are
+// the library's cached memory and go back with the step, so that any number of
+// batches and servers share them.  One step at a time: the caller has waited
+// for the step before.
 class StepRunner {
 public:
     // Enqueue the items' samples: tallies[0, slots * 16) receive their counts
@@ -61,13 +63,11 @@ public:
     void free(hipStream_t s);
 
 private:
-    bool grow(size_t table_bytes, uint64_t part, hipStream_t s);
+    bool grow(size_t table_bytes, hipStream_t s);
 
     char *d_tables = nullptr, *h_tables = nullptr;  // the parts' tables; h_ pinned
     size_t table_cap = 0;
-    char *d_order = nullptr;  // the sort's buffers, then the blocks' counts
-    uint64_t order_cap = 0;   // positions d_order holds
-    bool off = false;         // no memory for them
+    bool off = false;  // no memory for a step
 };
 
 }  // namespace pm
