@@ -268,7 +268,7 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
         if (it.count > kStepMax - samples) return PM_OK;
         samples += it.count;
     }
-    if (samples == 0 || off || !draw_order_enabled() || samples < draw_order_min()) return PM_OK;
+    if (samples == 0 || !draw_order_enabled() || samples < draw_order_min()) return PM_OK;
     const auto too_small = [&](uint64_t parts) {
         return parts > 1 && samples / parts < std::min<uint64_t>(draw_order_min(), kStepPartMin);
     };
@@ -281,6 +281,7 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
         return PM_OK;  // the id order needs no tables
     }
     if (too_small(parts.size())) return PM_OK;
+    if (memory.skip()) return PM_OK;
     size_t bytes = 0;
     uint64_t largest = 0;
     for (const HostPart &p : parts) {
@@ -293,9 +294,10 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
     const uint64_t cap = order_positions(largest);
     char *order = nullptr;
     if (!grow(bytes, s) || tmp.get(&order, draw_sort_bytes(cap) + 4 * kCountWords) != PM_OK) {
-        off = true;
+        memory.failed();
         return PM_OK;
     }
+    memory.succeeded();
     size_t at = 0;
     for (const HostPart &p : parts) {  // (both tables are multiples of 8 bytes)
         const size_t c = p.chunks.size() * sizeof(StepChunk);

@@ -4,6 +4,7 @@
 
 #include <vector>
 
+#include "backoff.hpp"
 #include "batch.hpp"
 
 namespace pm {
@@ -57,7 +58,8 @@ public:
     // (slot * 16 + tag * 8 + c; zero elsewhere).  No two items share a slot
     // and a sampler.  *done is false, and nothing is enqueued, where the step
     // is left to the id order: fewer than draw_order_min() samples or more
-    // than 2^40, draw order off, too many small items, or no memory.
+    // than 2^40, draw order off, too many small items, or no memory (after
+    // which up to Backoff::kMost steps are left out before the next try).
     pm_status run(const BatchGraph *graphs, std::vector<StepItem> &items, uint64_t *tallies, int64_t slots,
                   unsigned blocks, hipStream_t s, bool *done);
     void free(hipStream_t s);
@@ -67,7 +69,7 @@ private:
 
     char *d_tables = nullptr, *h_tables = nullptr;  // the parts' tables; h_ pinned
     size_t table_cap = 0;
-    bool off = false;  // no memory for a step
+    Backoff memory;  // after steps without memory for their buffers
 };
 
 }  // namespace pm
