@@ -451,8 +451,8 @@ pm_status pm_samples_for_error(double rel_err, double delta, double alpha, uint6
  * lane advances together (1, 2 or 4; more loads in flight per lane, more
  * registers; id-order launches only) and resident blocks per compute unit
  * (1..64; also the grid of the draw-ordered launches).  Tallies do not depend
- * on the shape.  Default 1 and 4 (the fastest measured on MI355X; at 4 the
- * draw-ordered launches take 6). */
+ * on the shape.  Until one is set: 1 and 4, draw-ordered launches 6 (the
+ * fastest measured on MI355X); a shape that is set holds for both orders. */
 pm_status pm_set_sampler_shape(int32_t samples_per_lane, int32_t blocks_per_cu);
 
 /* Draw-ordered sampling in pm_count, pm_sample_async, pm_count_alias, a batch's

@@ -7,6 +7,7 @@
 #include "graph.hpp"
 #include "profile.hpp"
 #include "sampler.hpp"
+#include "samplershape.hpp"
 #include "streams.hpp"
 
 #include <algorithm>
@@ -122,8 +123,7 @@ static pm_status sum_tallies(const uint64_t *parts_p, unsigned rows_p, const uin
 }
 
 // launch shape of the samplers (pm_set_sampler_shape)
-static std::atomic<int> g_samples_per_lane{1};
-static std::atomic<int> g_blocks_per_cu{4};
+static SamplerShape g_shape;
 static std::atomic<int> g_draw_order{1};  // draw-ordered sampling for large k (pm_set_draw_order)
 static std::atomic<uint64_t> g_draw_min{kSortedMinDefault};
 static std::atomic<int> g_search_mode{PM_SEARCH_HASH};  // adjacency tests (pm_set_search_mode)
@@ -155,8 +155,7 @@ pm_status set_sampler_shape(int32_t samples_per_lane, int32_t blocks_per_cu)
         set_error("sampler shape: samples_per_lane in {1,2,4}, blocks_per_cu in [1,64]");
         return PM_EINVAL;
     }
-    g_samples_per_lane.store(samples_per_lane);
-    g_blocks_per_cu.store(blocks_per_cu);
+    g_shape.set(samples_per_lane, blocks_per_cu);
     return PM_OK;
 }
 
@@ -186,14 +185,6 @@ int sampler_cu_count(int dev)
     return cache[dev];
 }
 
-// Blocks per compute unit of a draw-ordered launch at the default shape: its
-// blocks sweep one window of the graph together, so more of them hide more
-// latency without holding more of the graph.  1e7 + 1e7 samples took 1.33,
-// 1.21, 1.16 and 1.33 ms at 4, 5, 6 and 7 blocks on 1e6 edges, 1.66, 1.60,
-// 1.57 and 1.87 on 1e7, 2.56, 2.50, 2.51 and 3.01 on 1.2e8.  In id order 4
-// stay best (2e6 + 2e6 on 1e7 edges: 0.65 ms at 4, 0.69 at 6, 0.75 at 7).
-constexpr unsigned kOrderBlocksPerCu = 6;
-
 // The process-wide settings as one call uses them (read once, so that a
 // setter on another thread cannot change them between its launches).
 struct SampleShape {
@@ -203,9 +194,9 @@ struct SampleShape {
     bool order;
     uint64_t order_min;
     explicit SampleShape(const pm_graph *g)
-        : per_lane(g_samples_per_lane.load()), mode(g_search_mode.load()),
-          cap((unsigned)(sampler_cu_count(g->device) * g_blocks_per_cu.load())),
-          order_cap(cap == 4u * (unsigned)sampler_cu_count(g->device) ? cap / 4 * kOrderBlocksPerCu : cap), order(draw_order_enabled()),
+        : per_lane(g_shape.per_lane()), mode(g_search_mode.load()),
+          cap((unsigned)(sampler_cu_count(g->device) * g_shape.blocks())),
+          order_cap((unsigned)(sampler_cu_count(g->device) * g_shape.order_blocks())), order(draw_order_enabled()),
           order_min(draw_order_min())
     {
     }
