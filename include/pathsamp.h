@@ -324,9 +324,9 @@ pm_status pm_count_batch(const pm_graph *const *graphs, const pm_params *params,
  * runs requests in steps: each step samples a chunk of every active request,
  * in draw order from the samples of pm_set_draw_order on (with at most 0.3 GB
  * of buffers for the step, from the library's cached memory, beside the HBM
- * budget; without memory for them in id order), else as one persistent launch over work
- * tiles.  Requests that arrive while others run are admitted between steps
- * and share the device with them.  A request either
+ * budget; without memory for them in id order), else as one persistent launch
+ * over work tiles.  Requests that arrive while others run are admitted between
+ * steps and share the device with them.  A request either
  * gives its sample budgets or asks for a relative error: then its first
  * k_pilot ids per sampler are a pilot from which k is sized with
  * Corollary 5.3 (pm_samples_for_request) and the ids [k_pilot, k) follow.
@@ -545,7 +545,9 @@ pm_status pm_adjacent(const pm_graph *g, const int32_t *a, const int32_t *b, int
  * pm_profile_enable clears the totals and switches recording on (1) or off
  * (0); pm_profile_read waits for the recorded events and returns one entry
  * per kernel name (count = number of names, entries beyond capacity are
- * dropped).  Timing adds two event records per launch. */
+ * dropped).  Timing adds two event records per launch.  pm_count runs both
+ * samplers in one launch where the budgets are small: its time then stands
+ * under "sample_path" and under "sample_centered". */
 typedef struct {
     char name[48];
     uint64_t launches;

@@ -447,8 +447,8 @@ pm_status launch_alias(const pm_graph *g, bool centered, uint64_t seed, uint64_t
     return PM_OK;
 }
 
-pm_status sample_alias_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *, uint64_t *, bool *,
-                             hipStream_t s)
+pm_status sample_alias_async(const pm_graph *g, const pm_params *p, uint64_t *tallies_dev, uint64_t *, uint64_t *,
+                             bool *, hipStream_t s)
 {
     if ((g->R_tau && !g->alias_tau) || (g->R_lam && !g->alias_lam)) {
         set_error("alias draw: the graph has no alias tables (pm_graph_build_alias)");

@@ -76,8 +76,7 @@ constexpr int64_t kKeepTile = (int64_t)kBlock * kKeepItems;
 template <bool WRITE>
 __global__ __launch_bounds__(kBlock) void k_keep(const uint32_t *__restrict__ lo, const uint32_t *__restrict__ hi,
                                                  int64_t M, uint32_t *__restrict__ tile_sums,
-                                                 uint32_t *__restrict__ lo_out, uint32_t *__restrict__ hi_out,
-                                                 IngestState *st)
+                                                 uint32_t *__restrict__ lo_out, uint32_t *__restrict__ hi_out)
 {
     __shared__ uint32_t s_sum[kBlock / kWave];
     const int w = threadIdx.x / kWave, lane = lane_id();
@@ -256,11 +255,11 @@ pm_status csr_from_edges_impl(const pm_edge_view *ev, int64_t *off, int32_t *col
     {
         ProfScope prof("ingest.dedup", s);
         hipLaunchKernelGGL(k_keep<false>, dim3((unsigned)tiles), dim3(kBlock), 0, s, lo_s, hi_s, E, sums, nullptr,
-                           nullptr, st);
+                           nullptr);
         hipLaunchKernelGGL((scan_tiles_kernel<uint32_t, SumOp<uint32_t>>), dim3(1), dim3(1024), 0, s, sums, tiles,
                            SumOp<uint32_t>(), 0u, &st->kept);
-        hipLaunchKernelGGL(k_keep<true>, dim3((unsigned)tiles), dim3(kBlock), 0, s, lo_s, hi_s, E, sums, lo_u, hi_u,
-                           st);
+        hipLaunchKernelGGL(k_keep<true>, dim3((unsigned)tiles), dim3(kBlock), 0, s, lo_s, hi_s, E, sums, lo_u,
+                           hi_u);
         PM_HIP(hipGetLastError());
     }
     PM_HIP(hipMemcpyAsync(&hst, st, sizeof(hst), hipMemcpyDeviceToHost, s));
@@ -291,8 +290,7 @@ pm_status csr_from_edges_impl(const pm_edge_view *ev, int64_t *off, int32_t *col
         hipLaunchKernelGGL(k_row_starts, dim3(kb), dim3(kBlock), 0, s, hi_l, K, n, low);
         hipLaunchKernelGGL(k_offsets, dim3((unsigned)(n / kBlock + 1)), dim3(kBlock), 0, s, up, low, n, off);
         if (K > 0)
-            hipLaunchKernelGGL(k_place, dim3(kb), dim3(kBlock), 0, s, lo_u, hi_u,
-                               hi_l, lo_l, up, low, K, col);
+            hipLaunchKernelGGL(k_place, dim3(kb), dim3(kBlock), 0, s, lo_u, hi_u, hi_l, lo_l, up, low, K, col);
         PM_HIP(hipGetLastError());
     }
     *slots_out = slots;

@@ -843,16 +843,16 @@ __global__ __launch_bounds__(kBlock) void k_ladder_levels(const uint32_t *__rest
 // row's two bounds are one 8-byte load (3.20 -> 3.05 ms beside the row hash).
 // Batches of 8 keep four waves a SIMD; batches of 4 took 3.15 ms, of 16 (two
 // waves) 3.65 with the narrow loads.
-constexpr int kWItems = 16;
-constexpr int kWBatch = 8;
-static_assert((int64_t)kWave * kWItems == kPrefixSeg, "one wave per prefix segment");
-
 //
 // A slot's row comes from the segment's first row and the row starts inside
 // the segment, marked in a bitmap in LDS by the wave, instead of from an array
 // of rows: the row kernels write 8 bytes a slot less and this one reads 4 less
 // (R-MAT scale 22 from CSR to result: 11.03 -> 10.18 ms with the batches and
 // the wide loads).
+constexpr int kWItems = 16;
+constexpr int kWBatch = 8;
+static_assert((int64_t)kWave * kWItems == kPrefixSeg, "one wave per prefix segment");
+
 __global__ __launch_bounds__(kBlock) void k_weights_reduce(const uint32_t *__restrict__ col,
                                                            const uint32_t *__restrict__ seg_row,
                                                            const uint32_t *__restrict__ rev,

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(1024) void k_tally_sum(const unsigned long long *__
 // tallies[0..8) and [8..16) (3-path, centered): the sums of the rows of parts_p
 // and parts_c (a sampler that did not run has none)
 static pm_status sum_tallies(const uint64_t *parts_p, unsigned rows_p, const uint64_t *parts_c, unsigned rows_c,
-                      uint64_t *tallies, hipStream_t s)
+                             uint64_t *tallies, hipStream_t s)
 {
     hipLaunchKernelGGL(k_tally_sum, dim3(2), dim3(1024), 0, s, (const unsigned long long *)parts_p, rows_p,
                        (const unsigned long long *)parts_c, rows_c, (unsigned long long *)tallies);
@@ -270,9 +270,11 @@ static pm_status sample_chunk(const SampleShape &sh, const SamplerView &v, bool 
     const int mode = sh.mode;
     if (mode == PM_SEARCH_WAVE) {
         if (centered)
-            hipLaunchKernelGGL((k_sample_wave<true, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t, q);
+            hipLaunchKernelGGL((k_sample_wave<true, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t,
+                               q);
         else
-            hipLaunchKernelGGL((k_sample_wave<false, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t, q);
+            hipLaunchKernelGGL((k_sample_wave<false, true>), dim3(kb), dim3(kBlock), 0, s, v, seed, first, kc, ids, t,
+                               q);
     } else if (mode == PM_SEARCH_HASH) {
         if (centered)
             hipLaunchKernelGGL((k_sample_sorted<true, PM_SEARCH_HASH>), dim3(kb), dim3(kBlock), 0, s, v, seed, first,
@@ -536,7 +538,8 @@ static pm_status sample_into(const pm_graph *g, const pm_params *p, uint64_t *ta
     PM_TRY(check_device(g));
     const SampleShape sh(g);
     const bool pair = sh.one_chunk(g->R_tau, p->k_path) && sh.one_chunk(g->R_lam, p->k_cent);
-    if (std::max(sh.cap, sh.order_cap) > kMaxTallyParts || std::max(p->k_path, p->k_cent) > max_launch_samples(sh.cap) ||
+    if (std::max(sh.cap, sh.order_cap) > kMaxTallyParts ||
+        std::max(p->k_path, p->k_cent) > max_launch_samples(sh.cap) ||
         (!pair && (sh.sorted(g->R_tau, p->k_path) || sh.sorted(g->R_lam, p->k_cent))))
         scratch = nullptr;
     if (!scratch) PM_TRY(fill_async<uint64_t>(tallies_dev, 0ull, 2 * PM_NUM_TALLIES, s));

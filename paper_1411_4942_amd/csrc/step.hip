@@ -174,7 +174,8 @@ std::vector<HostPart> cut_parts(std::vector<StepItem> &items, uint64_t samples)
                 weights.push_back(it.R);
             }
             const uint64_t take = std::min<uint64_t>(it.count - done, per - p.samples);
-            p.chunks.push_back(StepChunk{it.first + done, it.seed, p.samples, it.slot, (uint32_t)p.groups.size() - 1, 0});
+            p.chunks.push_back(
+                StepChunk{it.first + done, it.seed, p.samples, it.slot, (uint32_t)p.groups.size() - 1, 0});
             p.samples += (uint32_t)take;
             done += take;
         }

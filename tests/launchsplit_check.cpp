@@ -10,7 +10,8 @@
 
 int main()
 {
-    const uint64_t ks[] = {1, 64, (1ull << 40) - 1, 1ull << 40, (1ull << 41) + 77, (1ull << 44) + 1, (1ull << 50) + 12345};
+    const uint64_t ks[] = {1,           64, (1ull << 40) - 1, 1ull << 40, (1ull << 41) + 77, (1ull << 44) + 1,
+                           (1ull << 50) + 12345};
     for (unsigned blocks : {1u, 32u, 128u, 256u, 1024u, 16384u})
         for (uint64_t k : ks)
             for (uint64_t U : {1u, 2u, 4u}) {
