@@ -275,63 +275,59 @@ pm_status StepRunner::run(const BatchGraph *graphs, std::vector<StepItem> &items
     };
     // (the least there can be, before the work of cutting them)
     if (too_small((items.size() + kStepChunks - 1) / kStepChunks)) return PM_OK;
-    std::vector<HostPart> parts;
-    try {
-        parts = cut_parts(items, samples);
-    } catch (const std::bad_alloc &) {
-        return PM_OK;  // the id order needs no tables
-    }
-    if (too_small(parts.size())) return PM_OK;
-    if (memory.skip()) return PM_OK;
-    size_t bytes = 0;
-    uint64_t largest = 0;
-    for (const HostPart &p : parts) {
-        bytes += table_bytes(p);
-        largest = std::max<uint64_t>(largest, p.samples);
-    }
-    // the sort's buffers, then the blocks' counts: the library's cached memory
-    // for the step, as pm_count's
-    Temps tmp(s);
-    const uint64_t cap = order_positions(largest);
-    char *order = nullptr;
-    if (!grow(bytes, s) || tmp.get(&order, draw_sort_bytes(cap) + 4 * kCountWords) != PM_OK) {
-        memory.failed();
-        return PM_OK;
-    }
-    memory.succeeded();
-    size_t at = 0;
-    for (const HostPart &p : parts) {  // (both tables are multiples of 8 bytes)
-        const size_t c = p.chunks.size() * sizeof(StepChunk);
-        std::memcpy(h_tables + at, p.chunks.data(), c);
-        std::memcpy(h_tables + at + c, p.groups.data(), p.groups.size() * sizeof(StepGroup));
-        at += table_bytes(p);
-    }
-    DrawSortBufs b{};
-    draw_sort_carve(order, cap, &b);
-    uint32_t *counts = reinterpret_cast<uint32_t *>(order + draw_sort_bytes(cap));
-    const auto enqueue = [&]() -> pm_status {
-        PM_HIP(hipMemcpyAsync(d_tables, h_tables, bytes, hipMemcpyHostToDevice, s));
-        PM_TRY(fill_async<uint64_t>(tallies, 0ull, slots * 2 * PM_NUM_TALLIES, s));
+    bool enqueued = false;
+    const auto step = [&]() -> pm_status {
+        const std::vector<HostPart> parts = cut_parts(items, samples);
+        if (too_small(parts.size()) || memory.skip()) return PM_OK;
+        size_t bytes = 0;
+        uint64_t largest = 0;
+        for (const HostPart &p : parts) {
+            bytes += table_bytes(p);
+            largest = std::max<uint64_t>(largest, p.samples);
+        }
+        // the sort's buffers, then the blocks' counts: the library's cached
+        // memory for the step, as pm_count's
+        Temps tmp(s);
+        const uint64_t cap = order_positions(largest);
+        char *order = nullptr;
+        if (!grow(bytes, s) || tmp.get(&order, draw_sort_bytes(cap) + 4 * kCountWords) != PM_OK) {
+            memory.failed();
+            return PM_OK;
+        }
+        memory.succeeded();
         size_t at = 0;
+        for (const HostPart &p : parts) {  // (both tables are multiples of 8 bytes)
+            const size_t c = p.chunks.size() * sizeof(StepChunk);
+            std::memcpy(h_tables + at, p.chunks.data(), c);
+            std::memcpy(h_tables + at + c, p.groups.data(), p.groups.size() * sizeof(StepGroup));
+            at += table_bytes(p);
+        }
+        DrawSortBufs b{};
+        draw_sort_carve(order, cap, &b);
+        uint32_t *counts = reinterpret_cast<uint32_t *>(order + draw_sort_bytes(cap));
+        enqueued = true;
+        PM_HIP(hipMemcpyAsync(d_tables, h_tables, at, hipMemcpyHostToDevice, s));
+        PM_TRY(fill_async<uint64_t>(tallies, 0ull, slots * 2 * PM_NUM_TALLIES, s));
+        at = 0;
         for (const HostPart &p : parts) {
             PM_TRY(launch_part(graphs, p, d_tables + at, b, counts, tallies, blocks, s));
             at += table_bytes(p);
         }
+        *done = true;
         return PM_OK;
     };
     pm_status st;
     try {
-        st = enqueue();
+        st = step();
     } catch (const std::bad_alloc &) {
+        if (!enqueued) return PM_OK;  // the id order needs no tables
         set_error("ordered step: no host memory");
         st = PM_ENOMEM;
     }
     // a step that failed midway has parts in flight: they read the tables, which
     // the next step writes, and the graphs, which the caller may then free
     if (st != PM_OK) (void)hipStreamSynchronize(s);
-    PM_TRY(st);
-    *done = true;
-    return PM_OK;
+    return st;
 }
 
 }  // namespace pm
